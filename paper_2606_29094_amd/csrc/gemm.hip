@@ -187,8 +187,8 @@ static hipError_t launch(const GemmPlan& p, const T* A, int lda, const T* B, int
 // times; charging both picked worse plans, e.g. 62 vs 52 us for the 512-row
 // MHA QKV projection). The cheapest
 // (configuration, split) wins. 128x192 with two blocks per CU (cfg 22) runs
-// without K splits only (its table holds unsplit launches); the small tiles
-// only for few rows. The eight-wave configurations run the split-phase tile
+// without K splits only (its table holds unsplit launches). Up to 1024 rows
+// the tables of kFewRowTables apply instead. The eight-wave configurations run the split-phase tile
 // form with a three-stage weight ring (6, 21, 70) or three stages of both
 // operands (29); their tables are the ones measured for their two-ring form,
 // each entry scaled by the time ratios of the forms measured at that k-tile
@@ -200,39 +200,41 @@ static hipError_t launch(const GemmPlan& p, const T* A, int lda, const T* B, int
 // 0.87-0.94 and 0.90-0.97).
 namespace {
 struct RoundTable {
-  int cfg, occ, max_m;
+  int cfg, occ;
   bool unsplit_only;
   int n;
   float kt[15], us[15];
   int min_kt = 0;          // used only for at least this many k-tiles per block
+  int max_m = 1 << 30;     // and for at most this many rows
 };
 const RoundTable kRoundTables[] = {
-    {6, 1, 1 << 30, false, 15,
+    {6, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {23.9f, 28.5f, 33.9f, 48.5f, 45.5f, 55.0f, 70.8f, 81.0f, 84.3f, 100.1f, 122.4f, 141.7f, 213.1f, 263.3f, 398.9f}},
-    {21, 1, 1 << 30, false, 15,
+    {21, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {18.2f, 23.6f, 26.3f, 38.7f, 37.9f, 43.6f, 56.3f, 64.7f, 67.5f, 80.5f, 95.1f, 118.5f, 175.2f, 223.3f, 343.0f}},
-    {22, 2, 1 << 30, true, 4, {56, 64, 192, 296}, {81.9f, 93.1f, 282.1f, 435.5f}},
-    {29, 1, 1 << 30, false, 15,
+    {22, 2, true, 4, {56, 64, 192, 296}, {81.9f, 93.1f, 282.1f, 435.5f}},
+    {29, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {15.2f, 17.6f, 21.0f, 28.5f, 27.5f, 33.1f, 42.6f, 49.1f, 51.6f, 63.0f, 74.3f, 89.6f, 131.7f, 168.7f, 249.4f}},
-    {42, 1, 1 << 30, false, 15,
+    {42, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {14.6f, 18.1f, 20.7f, 29.2f, 27.6f, 32.4f, 41.1f, 47.7f, 47.8f, 56.8f, 70.6f, 80.0f, 124.7f, 154.4f, 232.9f}},
-    {1, 2, 128, false, 15,
+    // (LM head only: the projections of up to 1024 rows use the tables below)
+    {1, 2, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
-     {17.1f, 22.4f, 25.6f, 37.3f, 33.5f, 40.8f, 51.1f, 65.7f, 65.8f, 71.1f, 90.8f, 119.1f, 171.0f, 214.9f, 335.1f}},
-    {10, 3, 64, false, 1, {64}, {75.0f}},
+     {17.1f, 22.4f, 25.6f, 37.3f, 33.5f, 40.8f, 51.1f, 65.7f, 65.8f, 71.1f, 90.8f, 119.1f, 171.0f, 214.9f, 335.1f},
+     0, 128},
     // 32x32x16 MFMA tiles: 256x128 with four 128x64-wave tiles, and 384x256
     // with eight 96x128-wave tiles (two waves per SIMD). Their round times
     // were measured against configurations 29 and 6 in the same runs (full
     // rounds, weights streamed from HBM) and scaled by those configurations'
     // tables above, so all tables share one measurement basis.
-    {62, 1, 1 << 30, false, 15,
+    {62, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {17.3f, 20.0f, 24.6f, 35.1f, 33.5f, 40.8f, 50.3f, 61.1f, 61.9f, 79.5f, 87.3f, 110.3f, 158.0f, 211.6f, 330.7f}},
-    {65, 1, 1 << 30, false, 15,
+    {65, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {37.4f, 46.5f, 57.2f, 79.0f, 73.6f, 88.7f, 118.5f, 131.5f, 126.5f, 156.3f, 204.0f, 238.4f, 360.9f, 430.0f, 679.5f},
      148},   // measured ahead only with long K walks (the GQA down projection); the
@@ -240,24 +242,80 @@ const RoundTable kRoundTables[] = {
     // 256x224: measured against configuration 6 in the same runs (one and two
     // full rounds per k-tile count) and scaled by that configuration's table;
     // a round takes 0.82-0.94 (mean 0.89) of a 256x256 round for 0.875 of its work
-    {70, 1, 1 << 30, false, 15,
+    {70, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {22.5f, 25.7f, 31.3f, 45.6f, 42.3f, 51.5f, 64.1f, 71.1f, 70.6f, 94.1f, 111.6f, 126.1f, 192.8f, 234.0f, 374.4f}},
 };
 
-double round_us(const RoundTable& t, double kt) {
-  if (kt <= t.kt[0]) return t.us[0] * kt / t.kt[0];
-  for (int i = 1; i < t.n; ++i)
-    if (kt <= t.kt[i]) {
-      const double w = (kt - t.kt[i - 1]) / (t.kt[i] - t.kt[i - 1]);
-      return t.us[i - 1] + w * (t.us[i] - t.us[i - 1]);
+// Launches of up to kFewRows (kernels.h) rows: every configuration that wins somewhere
+// there, timed in one run (MI355X, the eight projection shapes of both models,
+// 16 row counts from 8 to 1024, 1 to 8 K slices, weights streamed from HBM:
+// 7158 launches). us1[i] is the median time of a launch of 151 to 256 blocks
+// whose blocks walk kFewKt[i] k-tiles, us2 that of 384 to 512 blocks of the
+// configuration whose blocks fit twice on a CU (64 KB of LDS). Over the shapes
+// and row counts measured, the picks made from these tables take 0.9 % longer
+// than the best launch of each; the picks made from the tables above took
+// 21 % longer (33 % up to 192 rows). Above 1024 rows the launches run several
+// rounds of the large tiles, which is what the tables above describe.
+constexpr int kFewPoints = 15;
+const float kFewKt[kFewPoints] = {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296};
+struct FewRowTable {
+  int cfg, occ;
+  float us1[kFewPoints], us2[kFewPoints];
+};
+const FewRowTable kFewRowTables[] = {
+    {80, 2, {5.0f, 7.9f, 9.2f, 11.1f, 12.0f, 13.4f, 15.5f, 20.2f, 20.1f, 22.3f, 27.6f, 34.3f, 48.7f, 59.3f, 88.6f},
+     {9.3f, 11.7f, 12.6f, 21.1f, 17.9f, 20.2f, 28.7f, 31.7f, 25.7f, 36.3f, 45.8f, 41.7f, 82.6f, 76.5f, 111.9f}},
+    {81, 1, {5.9f, 9.3f, 10.1f, 13.3f, 14.9f, 19.3f, 20.5f, 23.2f, 25.2f, 30.2f, 32.4f, 42.1f, 63.5f, 79.3f, 115.1f}, {}},
+    {82, 1, {9.8f, 12.2f, 11.6f, 21.2f, 16.2f, 18.3f, 25.7f, 27.6f, 26.6f, 30.8f, 44.5f, 46.3f, 67.3f, 84.4f, 125.0f}, {}},
+    {83, 1, {9.4f, 13.5f, 14.5f, 21.5f, 20.2f, 20.7f, 26.6f, 35.0f, 38.6f, 39.2f, 47.4f, 56.2f, 99.0f, 100.9f, 183.2f}, {}},
+    {84, 1, {7.0f, 10.9f, 11.8f, 14.7f, 16.2f, 18.3f, 21.3f, 28.0f, 28.0f, 31.7f, 38.2f, 45.7f, 66.4f, 87.1f, 125.6f}, {}},
+    {85, 1, {10.8f, 13.0f, 12.9f, 23.1f, 18.0f, 21.1f, 28.2f, 29.6f, 29.2f, 33.3f, 46.6f, 51.0f, 73.6f, 91.2f, 132.3f}, {}},
+    {86, 1, {11.2f, 15.3f, 16.0f, 24.5f, 24.4f, 25.6f, 31.2f, 37.0f, 41.8f, 41.8f, 49.9f, 67.5f, 99.3f, 108.1f, 176.1f}, {}},
+    {87, 1, {7.8f, 12.2f, 13.0f, 16.4f, 18.1f, 20.9f, 24.0f, 30.8f, 32.0f, 36.3f, 41.6f, 50.1f, 74.9f, 102.0f, 149.9f}, {}},
+    {88, 1, {12.5f, 15.4f, 15.9f, 25.2f, 22.5f, 25.2f, 31.2f, 35.6f, 37.8f, 42.3f, 50.8f, 63.8f, 92.4f, 115.1f, 173.5f}, {}},
+    {89, 1, {13.6f, 16.4f, 17.7f, 26.5f, 24.4f, 27.0f, 33.3f, 39.4f, 40.1f, 45.8f, 55.8f, 68.8f, 101.1f, 123.1f, 184.9f}, {}},
+    {90, 1, {13.8f, 18.5f, 19.5f, 28.0f, 28.3f, 30.1f, 36.3f, 43.2f, 54.8f, 52.5f, 60.4f, 76.5f, 118.0f, 135.0f, 203.9f}, {}},
+    {92, 1, {16.7f, 17.5f, 21.0f, 28.4f, 25.4f, 27.7f, 35.3f, 41.8f, 38.9f, 48.2f, 59.5f, 68.9f, 98.1f, 115.6f, 169.2f}, {}},
+    {93, 1, {15.3f, 20.5f, 33.3f, 30.6f, 31.5f, 37.0f, 39.3f, 48.7f, 60.9f, 65.7f, 70.4f, 87.8f, 131.2f, 170.2f, 262.3f}, {}},
+    {29, 1, {18.4f, 19.9f, 24.0f, 31.7f, 29.5f, 32.3f, 39.3f, 50.1f, 53.2f, 56.3f, 71.4f, 83.2f, 120.9f, 156.9f, 241.9f}, {}},
+    {21, 1, {18.0f, 24.7f, 30.2f, 36.8f, 39.1f, 45.9f, 49.0f, 61.6f, 71.5f, 79.7f, 89.5f, 116.6f, 169.0f, 219.3f, 338.0f}, {}},
+    {70, 1, {19.4f, 28.7f, 30.9f, 39.5f, 45.7f, 50.6f, 65.2f, 69.6f, 77.2f, 84.8f, 106.1f, 125.4f, 193.3f, 250.7f, 386.6f}, {}},
+    {6, 1, {24.9f, 31.9f, 33.0f, 49.2f, 50.8f, 52.4f, 67.1f, 73.8f, 83.7f, 93.7f, 110.0f, 142.8f, 220.1f, 285.5f, 440.2f}, {}},
+};
+
+// linear in k-tiles between the points, proportional outside them
+double interp_us(const float* kts, const float* us, int n, double kt) {
+  if (kt <= kts[0]) return us[0] * kt / kts[0];
+  for (int i = 1; i < n; ++i)
+    if (kt <= kts[i]) {
+      const double w = (kt - kts[i - 1]) / (kts[i] - kts[i - 1]);
+      return us[i - 1] + w * (us[i] - us[i - 1]);
     }
-  return t.us[t.n - 1] * kt / t.kt[t.n - 1];
+  return us[n - 1] * kt / kts[n - 1];
 }
+
+// Modelled time of `units` blocks of kt k-tiles: whole rounds of one block (two
+// for occ 2) per CU; a partly filled round costs a whole one if it is the only
+// one and at least 0.85 of one after others (its blocks start as the round
+// before drains; 0.75 to 1 pick equally well).
+double few_rows_us(const FewRowTable& t, double kt, long units, int num_cu) {
+  const double a = interp_us(kFewKt, t.us1, kFewPoints, kt);
+  if (t.occ == 2) {
+    const double b = interp_us(kFewKt, t.us2, kFewPoints, kt);
+    const long full = units / (2L * num_cu), rem = units - full * 2L * num_cu;
+    return full * b + (rem == 0 ? 0.0 : (rem <= num_cu && full == 0 ? a : b));
+  }
+  const long full = units / num_cu, rem = units - full * num_cu;
+  if (rem == 0) return full * a;
+  return full == 0 ? a : (full + std::max(0.85, (double)rem / num_cu)) * a;
+}
+
+double round_us(const RoundTable& t, double kt) { return interp_us(t.kt, t.us, t.n, kt); }
 }  // namespace
 
 GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, bool allow_mf32,
-                   bool allow_tail, bool allow_odd) {
+                   bool allow_tail, bool allow_odd, int few_rows) {
   GemmPlan best{-1, 1, 0};
   if (M <= 0 || N <= 0) return best;
   if (es != 2 || K % 64 != 0) {
@@ -271,8 +329,36 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
     }
     return best;
   }
+  // time of the consumer's reads of the extra fp32 slices of a K split: few
+  // rows' slices come out of the caches (256 and 512 rows: 8 instead of 4
+  // slices cost the residual norm 1.7 us of 17 MB, 4 instead of 2 the RoPE
+  // kernel 4 us of 25 MB and the norm 1.5 us of 17 MB)
+  auto slice_us = [&](int s) {
+    return s > 1 ? (double)M * N * 4.0 * (s - 1) / (M <= few_rows ? 8.0e12 : 5.0e12) * 1e6 : 0.0;
+  };
   double best_t = 1e30;
+  if (M <= few_rows) {
+    for (const FewRowTable& c : kFewRowTables) {
+      if (!allow_odd && gemm_dl_odd(c.cfg)) continue;
+      int bm, bn, th;
+      gemm_dl_tile(c.cfg, &bm, &bn, &th);
+      // the small tiles reread the weights once per row tile: up to three
+      // (512 x 4096 x 4096 inside a step: 128x128 tiles 29.6 us and 256x128
+      // 23.6 us, 27 and 24 us alone with the activations in cache)
+      if (bm < 192 && ceil_div(M, bm) > 3) continue;
+      for (int s = 1; s <= 8; s *= 2) {
+        if (s > 1 && (!splittable || (K / 64) % s != 0 || K / s < 512)) continue;
+        const long units = (long)ceil_div(M, bm) * ceil_div(N, bn) * s;
+        const double t = few_rows_us(c, (double)(K / s) / 64.0, units, num_cu) + slice_us(s);
+        if (t < best_t * 0.999) {
+          best_t = t;
+          best = GemmPlan{c.cfg, s, 0};
+        }
+      }
+    }
+  }
   for (const RoundTable& c : kRoundTables) {
+    if (M <= few_rows) break;
     if (M > c.max_m) continue;
     if (!allow_mf32 && gemm_dl_mfma(c.cfg) == 32) continue;
     if (!allow_odd && gemm_dl_odd(c.cfg)) continue;
@@ -302,8 +388,7 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
           rounds += 1.0;
         }
       }
-      double t = rounds * round_us(c, (double)(K / s) / 64.0);
-      if (s > 1) t += (double)M * N * 4.0 * (s - 1) / 5.0e12 * 1e6;
+      const double t = rounds * round_us(c, (double)(K / s) / 64.0) + slice_us(s);
       if (t < best_t * 0.999) {
         best_t = t;
         best = GemmPlan{c.cfg, s, 0, sub, sub ? (int)rem : 0};
@@ -327,7 +412,10 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
 // 5.8 TB/s).
 GemmPlan lm_head_plan(int es, int M, int V, int K, int num_cu) {
   // the head's epilogue is 16x16 and keeps whole tiles (its partial results are per column tile)
-  GemmPlan p = gemm_plan(es, M, V, K, false, num_cu, false, false, false);
+  // It also runs many rounds at any row count, so the few-row tables (one
+  // round) do not describe it: their picks took 5-8 % longer at 65 to 128
+  // rows (100 rows, MHA 200 us against 210, GQA 234 against 248).
+  GemmPlan p = gemm_plan(es, M, V, K, false, num_cu, false, false, false, 0);
   if (p.cfg >= 0 && M <= 64) p = GemmPlan{((long)K * es) % 8192 == 0 ? 11 : 10, 1, 0};
   // The head is planned for its largest row count and skips, on the device,
   // the row tiles beyond the rows that need a prediction. The grouped order

@@ -29,9 +29,9 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int SA, int SB, int RB, int 
 __device__ __forceinline__ void dl_tile(char* smem, const bf16* __restrict__ A, int lda,
                                         const bf16* __restrict__ B, int ldb, int M, int N,
                                         int m0, int n0, int tn, int tz, int kbeg, int kend,
-                                        const Epi& epi) {
+                                        int rot, const Epi& epi) {
   static_assert(RB == 64 || RB == 128, "k-tile row bytes");
-  static_assert(SA >= 2 && SA <= 3 && SB >= SA && SB <= 4, "A and B stages");
+  static_assert(SA >= 2 && SA <= 4 && SB >= SA && SB <= 4, "A and B stages");
   static_assert(MF == 16 || MF == 32, "MFMA tile");
   constexpr int DA = SA - 1, DB = SB - 1;  // prefetch distances (k-tiles ahead)
   constexpr int NW = WAVES_M * WAVES_N;
@@ -62,13 +62,14 @@ __device__ __forceinline__ void dl_tile(char* smem, const bf16* __restrict__ A, 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int nkt = kend > kbeg ? (kend - kbeg) / BK : 0;
-  // K order: epilogues that ask for it (the LM head, which streams a large
-  // weight matrix with a 2^n-byte row pitch) start each column tile's K walk
-  // at a different k-tile (column tile mod k-tiles), so that the blocks in
-  // flight read different column offsets of their weight rows at any moment
-  // and spread over the HBM channels (MHA vocab head with 32 rows: 4.5 -> 5.9
-  // TB/s); the others walk K from the start.
-  const int krot = Epi::kRotateK && nkt > 0 ? tn % nkt : 0;
+  // K order: with rot (the LM head always; other launches by the rule in
+  // gemm_dl_launch) each column tile's K walk starts at a different k-tile
+  // (column tile mod k-tiles), so that the blocks in flight read different
+  // column offsets of their weight rows at any moment and spread over the HBM
+  // channels (MHA vocab head with 32 rows: 4.5 -> 5.9 TB/s); the others walk K
+  // from the start. Only the four-stage tiles take rot: deciding it at run
+  // time costs the large launches of the other tiles 1-2 %.
+  const int krot = (Epi::kRotateK || (SA == 4 && rot)) && nkt > 0 ? tn % nkt : 0;
   auto ktile = [&](int kt) { const int k = kt + krot; return k >= nkt ? k - nkt : k; };
 
   // LDS chunk slot of global chunk c in row r: c ^ swz(r). With 16x16x32
@@ -532,14 +533,14 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int SA, int SB, int RB, int 
 __device__ __forceinline__ void any_tile(char* smem, const bf16* __restrict__ A, int lda,
                                          const bf16* __restrict__ B, int ldb, int M, int N,
                                          int m0, int n0, int tn, int tz, int kbeg, int kend,
-                                         const Epi& epi) {
+                                         int rot, const Epi& epi) {
   if constexpr (SP) {
     static_assert(MF == 16 && RB == 128, "split-phase form: 16x16x32 tiles, 128-byte rows");
     dls_tile<BM, BN, WAVES_M, WAVES_N, SA, SB, Epi>(smem, A, lda, B, ldb, M, N, m0, n0, tn, tz,
                                                     kbeg, kend, epi);
   } else {
     dl_tile<BM, BN, WAVES_M, WAVES_N, SA, SB, RB, MF, Epi>(smem, A, lda, B, ldb, M, N, m0, n0, tn,
-                                                            tz, kbeg, kend, epi);
+                                                            tz, kbeg, kend, rot, epi);
   }
 }
 
@@ -567,7 +568,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int SA, int SB, int RB, int 
           bool TAIL, class Epi>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_kernel(
     const bf16* __restrict__ A, int lda, const bf16* __restrict__ B, int ldb, int M, int N,
-    int K, int k_per_split, int n_n, int n_m, int group_m, int n_tail, int sub, Epi epi) {
+    int K, int k_per_split, int n_n, int n_m, int group_m, int n_tail, int sub, int rot, Epi epi) {
   __shared__ __attribute__((aligned(1024))) char smem[(SA * BM + SB * BN) * RB];
   // Tile order. The logical order enumerates (K slice, row tile, column tile)
   // with the column tile fastest (group_m == 0), or, for weight matrices
@@ -635,21 +636,21 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_kernel(
       if (sub == 4) {
         any_tile<BM / 2, BN / 2, WAVES_M, WAVES_N, SA, SB, RB, MF, SP, Epi>(
             smem, A, lda, B, ldb, M, N, m0 + (part >> 1) * (BM / 2), n0 + (part & 1) * (BN / 2),
-            tn, tz, kbeg, kend, epi);
+            tn, tz, kbeg, kend, rot, epi);
         return;
       }
     }
     if constexpr (TAIL && Epi::kTailSplit && Sub::kHalf) {
       if (sub == 2) {
         any_tile<BM / 2, BN, WAVES_M, WAVES_N, SA, SB, RB, MF, SP, Epi>(
-            smem, A, lda, B, ldb, M, N, m0 + part * (BM / 2), n0, tn, tz, kbeg, kend, epi);
+            smem, A, lda, B, ldb, M, N, m0 + part * (BM / 2), n0, tn, tz, kbeg, kend, rot, epi);
         return;
       }
     }
     return;   // not reached: the launcher only splits where the shapes allow
   }
   any_tile<BM, BN, WAVES_M, WAVES_N, SA, SB, RB, MF, SP, Epi>(smem, A, lda, B, ldb, M, N, m0, n0, tn,
-                                                          tz, kbeg, kend, epi);
+                                                          tz, kbeg, kend, rot, epi);
 }
 
 // LM head over the rows that need a prediction only. The head is planned for
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_head_kernel(
     const int c = a / act;
     const int tn = c0 + c, tm = a - c * act;
     any_tile<BM, BN, WAVES_M, WAVES_N, SA, SB, RB, MF, SP, EpiLMHead>(
-        smem, A, lda, B, ldb, M, N, tm * BM, tn * BN, tn, 0, 0, K, epi);
+        smem, A, lda, B, ldb, M, N, tm * BM, tn * BN, tn, 0, 0, K, 1, epi);
     __syncthreads();   // the epilogue's LDS reads before the next tile's loads
   }
 }
@@ -689,7 +690,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_head_kernel(
 // four-wave tiles, one wave per SIMD, run slower in it and keep the two-ring
 // form). 256x224 (wave tiles of 64x112, seven column
 // fragments) covers a 3584-wide output in 16 column tiles, so that 4096 rows
-// make exactly one round of 256 tiles.
+// make exactly one round of 256 tiles. 80-93 serve the launches of up to 1024
+// rows: there the weights stream from HBM once and a launch is one round of
+// blocks, so the tile should hold every row (64 to 192) with a width that
+// makes close to 256 column tiles (24576 / 96 = 256, 37888 / 160 = 237), and
+// four equal stages of both operands keep three k-tiles (60-120 KB per CU) in
+// flight. Weight streaming measured at 32 rows, before -> after: gate/up
+// 24576x4096 51.0 -> 35.3 us (5.7 TB/s), QKV 22.9 -> 20.0, down 4096x12288
+// 22.5 -> 20.1; at 136 rows gate/up 37888x3584 72.6 -> 57.3 us, down
+// 3584x18944 45.9 -> 39.0; at 384 rows gate/up 24576x4096 79.2 -> 65.9 us
+// (192x192 split-phase).
 #define DL_CONFIGS(X)                      \
   X(1, 128, 128, 2, 2, 2, 2, 128, 16, 0)   \
   X(6, 256, 256, 2, 4, 2, 3, 128, 16, 1)   \
@@ -701,7 +711,20 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_head_kernel(
   X(42, 128, 192, 2, 2, 2, 3, 128, 16, 0)  \
   X(62, 256, 128, 2, 2, 2, 2, 128, 32, 0)  \
   X(65, 384, 256, 4, 2, 2, 2, 128, 32, 0)  \
-  X(70, 256, 224, 4, 2, 2, 3, 128, 16, 1)
+  X(70, 256, 224, 4, 2, 2, 3, 128, 16, 1)  \
+  X(80, 64, 64, 2, 2, 4, 4, 128, 16, 0)    \
+  X(81, 64, 96, 4, 1, 4, 4, 128, 16, 0)    \
+  X(82, 64, 128, 2, 2, 4, 4, 128, 16, 0)   \
+  X(83, 64, 160, 2, 5, 4, 4, 128, 16, 0)   \
+  X(84, 96, 96, 2, 3, 4, 4, 128, 16, 0)    \
+  X(85, 96, 128, 2, 4, 4, 4, 128, 16, 0)   \
+  X(86, 96, 160, 2, 5, 4, 4, 128, 16, 0)   \
+  X(87, 128, 96, 4, 1, 4, 4, 128, 16, 0)   \
+  X(88, 128, 128, 2, 2, 4, 4, 128, 16, 0)  \
+  X(89, 160, 128, 2, 4, 4, 4, 128, 16, 0)  \
+  X(90, 160, 160, 2, 5, 4, 4, 128, 16, 0)  \
+  X(92, 192, 128, 4, 2, 3, 3, 128, 16, 1)  \
+  X(93, 192, 192, 4, 2, 3, 3, 128, 16, 1)
 
 int gemm_dl_tile(int cfg, int* bm, int* bn, int* threads) {
   switch (cfg) {
@@ -777,14 +800,20 @@ hipError_t gemm_dl_launch(int cfg, const bf16* A, int lda, const bf16* B, int ld
       if (blocks >= (1L << 31)) return hipErrorInvalidValue;                             \
       Epi e = epi;                                                                       \
       e.set_mfma(MF_);                                                                   \
+      /* K rotation: one row tile (the activations stay in L2 whatever the */            \
+      /* walk) and weight rows a power of two apart, where blocks in step hit */         \
+      /* the same HBM channels (24576x4096 at 32 rows 44.5 -> 35.1 us, at 192 */         \
+      /* 52.8 -> 50.2; with two row tiles at 320 rows 63.4 -> 65.3; pitches of */        \
+      /* 3584 and 18944 elements are unchanged or up to 15 % slower) */                  \
+      const int rot = n_m == 1 && ldb >= 2048 && (ldb & (ldb - 1)) == 0;                 \
       if (n_tail == 0) {                                                                 \
         DLM_LAUNCH((gemm_dl_kernel<BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_, false, Epi>),   \
                    dim3(n_n, n_m, splits), dim3(WM_ * WN_ * 64), 0, st, A, lda, B, ldb, M, \
-                   N, K, kps, n_n, n_m, group_m, 0, 0, e);                               \
+                   N, K, kps, n_n, n_m, group_m, 0, 0, rot, e);                               \
       } else if constexpr (Epi::kTailSplit) {                                            \
         DLM_LAUNCH((gemm_dl_kernel<BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_, true, Epi>),    \
                    dim3((unsigned)blocks), dim3(WM_ * WN_ * 64), 0, st, A, lda, B, ldb, M, \
-                   N, K, kps, n_n, n_m, group_m, n_tail, sub, e);                        \
+                   N, K, kps, n_n, n_m, group_m, n_tail, sub, rot, e);                        \
       }                                                                                  \
       return hipGetLastError();                                                          \
     }                                                                                    \

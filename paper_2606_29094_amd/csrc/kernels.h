@@ -83,8 +83,11 @@ hipError_t gemm_debug_launch(int cfg, int epilogue, int sub, int n_tail, int gro
 // allow_tail: the last round may be split into sub-tiles (epilogues that allow it)
 // allow_odd: configurations whose wave tiles hold an odd number of column
 // fragments may be chosen (every epilogue but SwiGLU)
+// few_rows: launches of up to that many rows are planned from the few-row tables
+constexpr int kFewRows = 1024;
 GemmPlan gemm_plan(int elem_bytes, int M, int N, int K, bool splittable, int num_cu,
-                   bool allow_mf32 = true, bool allow_tail = true, bool allow_odd = true);
+                   bool allow_mf32 = true, bool allow_tail = true, bool allow_odd = true,
+                   int few_rows = kFewRows);
 // plan of the LM-head GEMM (M rows x V vocab entries)
 GemmPlan lm_head_plan(int elem_bytes, int M, int V, int K, int num_cu);
 template <typename T>
