@@ -22,8 +22,8 @@
 // folded in; P enters the PV product as the sum of two bf16 terms (about 16
 // significant bits), the output is rounded to bf16.
 //
-// fp32 path: a plain per-query-row kernel (one lane per query row) over LDS
-// tiles; it serves the small fp32 model.
+// fp32 path: attn_f32_kernel, on v_mfma_f32_16x16x4_f32; it serves the small
+// fp32 model.
 #include "common.h"
 #include "kernels.h"
 
@@ -47,8 +47,6 @@ __device__ __forceinline__ void split_p8(const f32x4& a, const f32x4& b, bf16x8&
   }
 }
 
-
-constexpr int kKeyTile = 64;
 
 // Wave layout: QG query groups of 16 rows x KG key groups. A block stages
 // key tiles of 64 * KG positions; key group kg works on keys [64 kg, 64 kg +
@@ -561,65 +559,126 @@ __global__ __launch_bounds__(GH* QG * 64) void attn_gqa_kernel(StepPlan p, const
   }
 }
 
-// fp32: one lane per query row; K and V^T tiles staged in LDS.
+// fp32 (the small fp32 model): one block = 16 query rows of one request x one
+// query head, kF32Waves waves that take 32-key groups in turn, each with its own
+// online softmax, merged in LDS at the end. Scores and outputs go through
+// v_mfma_f32_16x16x4_f32 as S^T = K Q^T and O^T = V^T P^T: a lane's score
+// accumulators (keys 4 g .. 4 g + 3 of a 16-key group, its own query; g = lane /
+// 16) are the B operands of the PV products as they stand, and K rows and
+// transposed V rows are read from the cache as the 16-byte fragments the MFMAs
+// take, without LDS (a block reads each once). Latency bounds it at the sizes the
+// model runs: 128 rows over 128 keys, 4 heads, took 324 us with one lane per query
+// row in 8 blocks of one wave, and takes 9 us.
+constexpr int kF32Waves = 4;
 template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(StepPlan p, const float* __restrict__ q,
-                                                      const float* __restrict__ kc,
-                                                      const float* __restrict__ vc, int s_max,
-                                                      int hq, int hkv, float* __restrict__ out,
-                                                      float scale) {
-  __shared__ float ks[kKeyTile][DH + 1];
-  __shared__ float vs[DH][kKeyTile + 1];
+__global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
+    StepPlan p, const float* __restrict__ q, const float* __restrict__ kc,
+    const float* __restrict__ vc, int s_max, int hq, int hkv, float* __restrict__ out,
+    float scale) {
+  constexpr int NDB = DH / 16;             // 16-wide dh groups
+  __shared__ float xm[kF32Waves][64], xl[kF32Waves][64];
+  __shared__ f32x4 xo[kF32Waves][NDB][64];
   const int tile = blockIdx.x, h = blockIdx.y;
-  const int r = plan_req_of_tile(p, tile);
+  int r = 0, t0 = 0;                       // request of this tile: 16-row tiles, request by request
+  for (; r + 1 < p.n_req; ++r) {
+    const int nt = (p.r[r].nrows + 15) / 16;
+    if (tile < t0 + nt) break;
+    t0 += nt;
+  }
   const ReqPlan& rq = p.r[r];
-  const int lrow0 = (tile - rq.tile0) * kQTile;
-  const int nvalid = min(kQTile, rq.nrows - lrow0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int g = lane >> 4, c = lane & 15;
+  const int qr = (tile - t0) * 16 + c;     // query row of this lane within the request
+  const bool q_ok = qr < rq.nrows;
+  const long qrow = rq.row0 + min(qr, rq.nrows - 1);
   const int L = rq.seq_len;
   const int kvh = h / (hq / hkv);
   const float* kb = kc + ((long)(rq.slot * hkv + kvh) * s_max) * DH;
   const float* vb = vc + ((long)(rq.slot * hkv + kvh) * DH) * s_max;
-  const int lane = threadIdx.x;
-  const bool q_ok = lane < nvalid;
-  const long qrow = rq.row0 + lrow0 + lane;
-  float qv[DH], acc[DH];
+
+  // a lane's fragment element e of dh group j is dh index 16 j + 4 g + e, for Q and K alike
+  f32x4 qf[NDB], o[NDB];
 #pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    qv[d] = q_ok ? q[qrow * hq * DH + h * DH + d] : 0.f;
-    acc[d] = 0.f;
+  for (int j = 0; j < NDB; ++j) {
+    qf[j] = *reinterpret_cast<const f32x4*>(q + qrow * hq * DH + h * DH + 16 * j + 4 * g);
+    o[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  float m_run = -INFINITY, l_run = 0.f;
-  for (int key0 = 0; key0 < L; key0 += kKeyTile) {
-    __syncthreads();
-    for (int c = lane; c < kKeyTile * DH; c += 64) {
-      const int kk = c / DH, d = c % DH;
-      ks[kk][d] = key0 + kk < L ? kb[(long)(key0 + kk) * DH + d] : 0.f;
-    }
-    for (int c = lane; c < kKeyTile * DH; c += 64) {
-      const int d = c / kKeyTile, kk = c % kKeyTile;
-      vs[d][kk] = key0 + kk < L ? vb[(long)d * s_max + key0 + kk] : 0.f;
-    }
-    __syncthreads();
-    const int nk = min(kKeyTile, L - key0);
-    for (int kk = 0; kk < nk; ++kk) {
-      float s = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;    // l: this lane's keys only
+  // 32-key groups; a slot holds a multiple of 64 positions, so reads past L stay inside it
+  for (int key0 = wave * 32; key0 < L; key0 += kF32Waves * 32) {
+    f32x4 s[2], vf[2][NDB];
 #pragma unroll
-      for (int d = 0; d < DH; ++d) s += qv[d] * ks[kk][d];
-      s *= scale;
-      const float m_new = fmaxf(m_run, s);
-      const float alpha = expf(m_run - m_new);
-      const float e = expf(s - m_new);
-      l_run = l_run * alpha + e;
+    for (int b = 0; b < 2; ++b) {
+      f32x4 kf[NDB];
 #pragma unroll
-      for (int d = 0; d < DH; ++d) acc[d] = acc[d] * alpha + e * vs[d][kk];
-      m_run = m_new;
+      for (int j = 0; j < NDB; ++j)
+        kf[j] = *reinterpret_cast<const f32x4*>(kb + (long)(key0 + 16 * b + c) * DH + 16 * j + 4 * g);
+      s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NDB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[b] = mfma16_f32(kf[j][e], qf[j][e], s[b]);
     }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int j = 0; j < NDB; ++j)
+        vf[b][j] = *reinterpret_cast<const f32x4*>(vb + (long)(16 * j + c) * s_max + key0 + 16 * b + 4 * g);
+    float mt = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = key0 + 16 * b + 4 * g + e < L;
+        s[b][e] = in ? s[b][e] * scale : -INFINITY;
+        mt = fmaxf(mt, s[b][e]);
+        if (!in) {                         // stale memory past the sequence: 0 x NaN is NaN
+#pragma unroll
+          for (int j = 0; j < NDB; ++j) vf[b][j][e] = 0.f;
+        }
+      }
+    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+    const float m_new = fmaxf(m_run, mt);  // finite: key0 < L
+    const float alpha = expf(m_run - m_new);
+    l_run *= alpha;
+#pragma unroll
+    for (int j = 0; j < NDB; ++j) o[j] *= alpha;
+    m_run = m_new;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float w = expf(s[b][e] - m_new);
+        l_run += w;
+#pragma unroll
+        for (int j = 0; j < NDB; ++j) o[j] = mfma16_f32(vf[b][j][e], w, o[j]);
+      }
   }
-  if (q_ok) {
-    float* dst = out + qrow * hq * DH + h * DH;
-    const float inv = 1.0f / l_run;
+  // merge the waves' key groups (wave 0 always has keys)
+  xm[wave][lane] = m_run;
+  xl[wave][lane] = l_run;
 #pragma unroll
-    for (int d = 0; d < DH; ++d) dst[d] = acc[d] * inv;
+  for (int j = 0; j < NDB; ++j) xo[wave][j][lane] = o[j];
+  __syncthreads();
+  float mm = -INFINITY;
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) mm = fmaxf(mm, xm[w][lane]);
+  float a[kF32Waves], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < kF32Waves; ++w) {
+    a[w] = expf(xm[w][lane] - mm);         // 0 for a wave without keys
+    l += xl[w][lane] * a[w];
+  }
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  const float inv = 1.0f / l;
+  for (int j = wave; j < NDB; j += kF32Waves) {
+    f32x4 t = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w) t += xo[w][j][lane] * a[w];
+    if (q_ok)
+      *reinterpret_cast<f32x4*>(out + qrow * hq * DH + h * DH + 16 * j + 4 * g) = t * inv;
   }
 }
 
@@ -695,12 +754,14 @@ hipError_t attention<float>(const StepPlan& p, const float* q, const float* kc, 
                             int s_max, int hq, int hkv, int dh, float* out, hipStream_t st) {
   if (p.n_tiles == 0) return hipSuccess;
   const float scale = 1.0f / sqrtf((float)dh);
-  dim3 g(p.n_tiles, hq);
+  int tiles = 0;
+  for (int r = 0; r < p.n_req; ++r) tiles += (p.r[r].nrows + 15) / 16;
+  dim3 g(tiles, hq);
   if (dh == 64)
-    DLM_LAUNCH(attn_f32_kernel<64>, g, dim3(64), 0, st, p, q, kc, vc, s_max, hq, hkv,
+    DLM_LAUNCH(attn_f32_kernel<64>, g, dim3(kF32Waves * 64), 0, st, p, q, kc, vc, s_max, hq, hkv,
                        out, scale);
   else if (dh == 128)
-    DLM_LAUNCH(attn_f32_kernel<128>, g, dim3(64), 0, st, p, q, kc, vc, s_max, hq, hkv,
+    DLM_LAUNCH(attn_f32_kernel<128>, g, dim3(kF32Waves * 64), 0, st, p, q, kc, vc, s_max, hq, hkv,
                        out, scale);
   else
     return hipErrorInvalidValue;

@@ -129,6 +129,63 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(
       (int)blockIdx.z);
 }
 
+// fp32 launches of few tiles: a block of kSmallWaves waves computes a 16 x 32
+// output tile, wave w multiplying the 16-wide k groups w, w + kSmallWaves, ...
+// straight from global memory (both operands are cache-resident at these sizes
+// and a block reads each fragment once, so LDS staging would only add barriers),
+// and wave 0 sums the waves' partials in wave order before the epilogue. What
+// bounds these launches is the serial walk over K, not bandwidth: with 128 rows
+// the 128x128 tiles of the kernel above are 2 blocks for a 256-wide output (49
+// us at K = 688) and 11 for the gate/up GEMM (24 us); these are 64 and 344
+// blocks (6 and 7 us).
+constexpr int kSmallWaves = 8;
+template <class Epi>
+__global__ __launch_bounds__(kSmallWaves * 64) void gemm_f32_small_kernel(
+    const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int M, int N,
+    int K, Epi epi) {
+  constexpr int FN = 2, UNR = 3;           // column fragments; k groups in flight per wave
+  __shared__ f32x4 part[kSmallWaves][FN][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = blockIdx.x * 16 * FN, m0 = blockIdx.y * 16;
+  // element e of a lane's fragment of k group c is k = 16 c + 4 (lane / 16) + e, for A and B alike
+  const float* a = A + (long)min(m0 + (lane & 15), M - 1) * lda + 4 * (lane >> 4);
+  const float* b[FN];
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn)
+    b[fn] = B + (long)epi.b_row(min(n0 + 16 * fn + (lane & 15), N - 1)) * ldb + 4 * (lane >> 4);
+  f32x4 acc[1][FN];
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) acc[0][fn] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nc = K / 16;
+  for (int c0 = wave; c0 < nc; c0 += kSmallWaves * UNR) {
+    f32x4 av[UNR], bv[UNR][FN];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int c = min(c0 + u * kSmallWaves, nc - 1);   // past the end: loaded, not used
+      av[u] = *reinterpret_cast<const f32x4*>(a + 16 * c);
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn) bv[u][fn] = *reinterpret_cast<const f32x4*>(b[fn] + 16 * c);
+    }
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      if (c0 + u * kSmallWaves >= nc) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) acc[0][fn] = mfma16_f32(av[u][e], bv[u][fn][e], acc[0][fn]);
+    }
+  }
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn) part[wave][fn][lane] = acc[0][fn];
+  __syncthreads();
+  if (wave != 0) return;
+#pragma unroll
+  for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+    for (int w = 1; w < kSmallWaves; ++w) acc[0][fn] += part[w][fn][lane];
+  epi(acc, m0, n0, lane, 0, nullptr, 1, 16, m0, (int)blockIdx.x, 0);
+}
+
 // --------------------------------------------------------------- launch --
 
 // Register-staged kernel: any K that is a multiple of 16 bytes, fp32 or bf16.
@@ -163,6 +220,13 @@ static hipError_t launch(const GemmPlan& p, const T* A, int lda, const T* B, int
     if (p.cfg >= 0)
       return gemm_dl_launch<Epi>(p.cfg, A, lda, B, ldb, M, N, K, p.splits, p.group_m,
                                  Epi::kTailSplit ? p.sub : 0, p.n_tail, epi, st);
+  } else if constexpr (Epi::kWaveLocal) {
+    if (p.cfg == kSmallF32 && M > 0 && N > 0) {
+      if (K % 16 != 0 || p.splits != 1) return hipErrorInvalidValue;
+      DLM_LAUNCH((gemm_f32_small_kernel<Epi>), dim3(ceil_div(N, 32), ceil_div(M, 16)),
+                 dim3(kSmallWaves * 64), 0, st, A, lda, B, ldb, M, N, K, epi);
+      return hipGetLastError();
+    }
   }
   return launch_rs<T, Epi>(A, lda, B, ldb, M, N, K, p.splits, epi, st);
 }
@@ -315,13 +379,19 @@ double round_us(const RoundTable& t, double kt) { return interp_us(t.kt, t.us, t
 }  // namespace
 
 GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, bool allow_mf32,
-                   bool allow_tail, bool allow_odd, int few_rows) {
+                   bool allow_tail, bool allow_odd, int few_rows, bool allow_small) {
   GemmPlan best{-1, 1, 0};
   if (M <= 0 || N <= 0) return best;
   if (es != 2 || K % 64 != 0) {
+    const int bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
+    const long tiles = (long)ceil_div(N, 128) * ceil_div(M, bm);
+    // (16 MB: the weights it was measured with, 0.26-1.4 MB, and others that
+    // stay in cache; larger ones stream, which the staged kernel's K split does)
+    if (es == 4 && K % 16 == 0 && allow_small && tiles < num_cu && (long)N * K * es <= 16L << 20) {
+      best.cfg = kSmallF32;
+      return best;
+    }
     if (splittable) {
-      int bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
-      long tiles = (long)ceil_div(N, 128) * ceil_div(M, bm);
       int s = 1;
       while (tiles * s < 2L * num_cu && K % (s * 2 * 64) == 0 && K / (s * 2) >= 512 && s < 8)
         s *= 2;
@@ -415,7 +485,7 @@ GemmPlan lm_head_plan(int es, int M, int V, int K, int num_cu) {
   // It also runs many rounds at any row count, so the few-row tables (one
   // round) do not describe it: their picks took 5-8 % longer at 65 to 128
   // rows (100 rows, MHA 200 us against 210, GQA 234 against 248).
-  GemmPlan p = gemm_plan(es, M, V, K, false, num_cu, false, false, false, 0);
+  GemmPlan p = gemm_plan(es, M, V, K, false, num_cu, false, false, false, 0, false);
   if (p.cfg >= 0 && M <= 64) p = GemmPlan{((long)K * es) % 8192 == 0 ? 11 : 10, 1, 0};
   // The head is planned for its largest row count and skips, on the device,
   // the row tiles beyond the rows that need a prediction. The grouped order

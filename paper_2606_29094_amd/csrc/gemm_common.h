@@ -52,6 +52,7 @@ struct EpiStore {
   static constexpr bool kMf32 = true;
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
+  static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
   __host__ __device__ void set_mfma(int) {}
   __device__ int b_row(int n) const { return n; }
   __device__ bool skip_tile(int) const { return false; }
@@ -97,6 +98,7 @@ struct EpiScaledStore {
   static constexpr bool kMf32 = false;
   static constexpr bool kTailSplit = false;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
+  static constexpr bool kWaveLocal = false;
   __host__ __device__ void set_mfma(int) {}
   template <int FM, int FN>
   __device__ void op32(f32x16 (&)[FM][FN], int, int, int, int) const {}
@@ -129,6 +131,7 @@ struct EpiAdd {
   static constexpr bool kMf32 = true;
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
+  static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
   __host__ __device__ void set_mfma(int) {}
   __device__ int b_row(int n) const { return n; }
   __device__ bool skip_tile(int) const { return false; }
@@ -202,6 +205,7 @@ struct EpiSwiGLU {
     return ((n >> wsh) & 1) ? F + f : f;
   }
   __device__ bool skip_tile(int) const { return false; }
+  static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
   static constexpr bool kRotateK = false;
   static constexpr bool kMf32 = true;
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
@@ -282,6 +286,7 @@ struct EpiLMHead {
   static constexpr bool kMf32 = false;
   static constexpr bool kTailSplit = false;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
+  static constexpr bool kWaveLocal = false;
   __host__ __device__ void set_mfma(int) {}
   template <int FM, int FN>
   __device__ void op32(f32x16 (&)[FM][FN], int, int, int, int) const {}

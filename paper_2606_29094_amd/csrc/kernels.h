@@ -48,7 +48,7 @@ __device__ __forceinline__ int plan_req_of_tile(const StepPlan& p, int tile) {
 
 // ---- GEMM family (gemm.hip, gemm_dl.hip) ----
 // cfg >= 0: a direct-load tile configuration (bf16); cfg < 0: register-staged
-// kernel. splits: number of K slices (fp32 partial slices, summed by the consumer).
+// kernel (kSmallF32: the small-tile fp32 kernel). splits: number of K slices (fp32 partial slices, summed by the consumer).
 // group_m: tile order (0 = plain); sub, n_tail: the last n_tail tiles of the
 // order are each run as `sub` (2 or 4) sub-tiles (0: none); active_cus > 0
 // (LM head over several row tiles only): one launch of blocks on that many
@@ -85,9 +85,13 @@ hipError_t gemm_debug_launch(int cfg, int epilogue, int sub, int n_tail, int gro
 // fragments may be chosen (every epilogue but SwiGLU)
 // few_rows: launches of up to that many rows are planned from the few-row tables
 constexpr int kFewRows = 1024;
+// allow_small: fp32 launches whose 128-wide tiles would not fill the CUs may use
+// the 16x32-tile kernel (plan cfg kSmallF32; every epilogue that needs only its
+// own wave)
+constexpr int kSmallF32 = -2;
 GemmPlan gemm_plan(int elem_bytes, int M, int N, int K, bool splittable, int num_cu,
                    bool allow_mf32 = true, bool allow_tail = true, bool allow_odd = true,
-                   int few_rows = kFewRows);
+                   int few_rows = kFewRows, bool allow_small = true);
 // plan of the LM-head GEMM (M rows x V vocab entries)
 GemmPlan lm_head_plan(int elem_bytes, int M, int V, int K, int num_cu);
 template <typename T>
