@@ -82,12 +82,8 @@ __global__ __launch_bounds__(QG* KG * 64) void attn_bf16_kernel(StepPlan p, cons
   // different heads, so the query tiles of one head share one XCD's L2
   const int h = blockIdx.x, tile = blockIdx.y;
   // request of this tile: tiles of QT rows are numbered request by request
-  int r = 0, t0 = 0;
-  for (; r + 1 < p.n_req; ++r) {
-    const int nt = (p.r[r].nrows + QT - 1) / QT;
-    if (tile < t0 + nt) break;
-    t0 += nt;
-  }
+  int t0;
+  const int r = plan_req_of_qtile(p, tile, QT, &t0);
   const ReqPlan& rq = p.r[r];
   const int lrow0 = (tile - t0) * QT;
   const int nvalid = min(QT, rq.nrows - lrow0);
@@ -381,12 +377,8 @@ __global__ __launch_bounds__(GH* QG * 64) void attn_gqa_kernel(StepPlan p, const
     tile = lid - kvh * n_tiles;
   }
   // request of this tile: tiles of QT rows are numbered request by request
-  int r = 0, t0 = 0;
-  for (; r + 1 < p.n_req; ++r) {
-    const int nt = (p.r[r].nrows + QT - 1) / QT;
-    if (tile < t0 + nt) break;
-    t0 += nt;
-  }
+  int t0;
+  const int r = plan_req_of_qtile(p, tile, QT, &t0);
   const ReqPlan& rq = p.r[r];
   const int lrow0 = (tile - t0) * QT;
   const int nvalid = min(QT, rq.nrows - lrow0);
@@ -579,12 +571,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
   __shared__ float xm[kF32Waves][64], xl[kF32Waves][64];
   __shared__ f32x4 xo[kF32Waves][NDB][64];
   const int tile = blockIdx.x, h = blockIdx.y;
-  int r = 0, t0 = 0;                       // request of this tile: 16-row tiles, request by request
-  for (; r + 1 < p.n_req; ++r) {
-    const int nt = (p.r[r].nrows + 15) / 16;
-    if (tile < t0 + nt) break;
-    t0 += nt;
-  }
+  int t0;
+  const int r = plan_req_of_qtile(p, tile, 16, &t0);
   const ReqPlan& rq = p.r[r];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, c = lane & 15;

@@ -34,15 +34,32 @@ struct StepPlan {
   ReqPlan r[kMaxReq];
 };
 
-// Row -> request lookup (requests are few; plan rows are ascending).
+// Request of a packed row, of a 64-row tile, or of a tile of qt rows (tiles
+// numbered request by request; *t0: the request's first tile). Every lane of
+// the wave must be active: lane l looks at request l and a ballot counts those
+// that start at or before the row. (A walk over the requests is up to 64
+// dependent loads at the start of each block: 64 requests of 64 rows, RoPE and
+// key/value write 34 -> 20 us, attention 123 -> 117.)
+static_assert(kMaxReq <= 64, "one lane per request");
 __device__ __forceinline__ int plan_req_of_row(const StepPlan& p, int row) {
-  int r = 0;
-  while (r + 1 < p.n_req && p.r[r + 1].row0 <= row) ++r;
-  return r;
+  const int lane = threadIdx.x & 63;
+  return __popcll(__ballot(lane < p.n_req && p.r[lane].row0 <= row)) - 1;
 }
 __device__ __forceinline__ int plan_req_of_tile(const StepPlan& p, int tile) {
-  int r = 0;
-  while (r + 1 < p.n_req && p.r[r + 1].tile0 <= tile) ++r;
+  const int lane = threadIdx.x & 63;
+  return __popcll(__ballot(lane < p.n_req && p.r[lane].tile0 <= tile)) - 1;
+}
+__device__ __forceinline__ int plan_req_of_qtile(const StepPlan& p, int tile, int qt, int* t0) {
+  const int lane = threadIdx.x & 63;
+  const int nt = lane < p.n_req ? (p.r[lane].nrows + qt - 1) / qt : 0;
+  int incl = nt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += v;
+  }
+  const int r = __popcll(__ballot(lane < p.n_req && incl <= tile));
+  *t0 = __builtin_amdgcn_readlane(incl - nt, r);
   return r;
 }
 
@@ -113,9 +130,12 @@ hipError_t gemm_lm_head(const GemmPlan& p, const T* U, int ldu, const T* W, int 
                         const int* m_count, hipStream_t st);
 
 // ---- per-row kernels (rowwise.hip) ----
+// the step's first kernel: h = embedding rows, out = rmsnorm(h) * g, cs = rotary table
 template <typename T>
-hipError_t embed_rows(const StepPlan& p, const T* E, int d, int vocab, int mask_id,
-                      const int32_t* tokens, const uint8_t* mask, float* h, hipStream_t st);
+hipError_t embed_norm_rows(const StepPlan& p, const T* E, int d, int vocab, int mask_id,
+                           const int32_t* tokens, const uint8_t* mask, const float* g, float eps,
+                           int head_dim, float theta, float* h, T* out, float2* cs,
+                           hipStream_t st);
 template <typename T>
 hipError_t rmsnorm_rows(const float* h, const float* g, int n, int d, float eps, T* out,
                         hipStream_t st);
@@ -123,7 +143,6 @@ hipError_t rmsnorm_rows(const float* h, const float* g, int n, int d, float eps,
 template <typename T>
 hipError_t add_rmsnorm_rows(float* h, const float* part, int splits, long stride, const float* g,
                             int n, int d, float eps, T* out, hipStream_t st);
-hipError_t rope_table(const StepPlan& p, int head_dim, float theta, float2* cs, hipStream_t st);
 template <typename T>
 hipError_t qkv_rope_scatter(const StepPlan& p, const float* qkv, int splits, long split_stride,
                             const float2* cs, int hq, int hkv, int dh, T* q_out,
@@ -134,6 +153,7 @@ template <typename T>
 hipError_t final_norm_gather(const float* h, const float* g, const int* lm_rows,
                              const int* lm_count, int m_max, int d, float eps, T* u,
                              hipStream_t st);
+// lm_count: device-side number of rows (nullptr: m_max)
 hipError_t lm_combine(const float* pm, const float* ps, const int* pi, int tiles, int ld,
                       const int* lm_count, int m_max, float* conf, int* tok, hipStream_t st);
 hipError_t unmask_select(const StepPlan& p, const float* conf, const int* tok,

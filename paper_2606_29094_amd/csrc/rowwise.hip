@@ -9,34 +9,6 @@
 
 namespace dlm {
 
-// ------------------------------------------------------------ embedding --
-// h[n] = E[mask ? mask_id : token] for every recompute row n (fp32 residual).
-// Token ids outside [0, vocab) are read as [MASK].
-template <typename T>
-__global__ void embed_kernel(StepPlan p, const T* __restrict__ E, int d, int vocab, int mask_id,
-                             const int32_t* __restrict__ tokens, const uint8_t* __restrict__ mask,
-                             float* __restrict__ h) {
-  const int n = blockIdx.x;
-  const int r = plan_req_of_row(p, n);
-  const ReqPlan& q = p.r[r];
-  const int pos = q.pos0 + (n - q.row0);
-  const long ti = (long)q.tok_off + pos;
-  const int tk = tokens[ti];
-  const int id = (mask[ti] || tk < 0 || tk >= vocab) ? mask_id : tk;
-  const T* src = E + (long)id * d;
-  float* dst = h + (long)n * d;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) dst[j] = to_f32(src[j]);
-}
-
-template <typename T>
-hipError_t embed_rows(const StepPlan& p, const T* E, int d, int vocab, int mask_id,
-                      const int32_t* tokens, const uint8_t* mask, float* h, hipStream_t st) {
-  if (p.n_rows == 0) return hipSuccess;
-  DLM_LAUNCH(embed_kernel<T>, dim3(p.n_rows), dim3(256), 0, st, p, E, d, vocab, mask_id,
-                     tokens, mask, h);
-  return hipGetLastError();
-}
-
 // -------------------------------------------------------------- rmsnorm --
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
   v = wave_sum(v);
@@ -179,6 +151,113 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float* __restrict__ h,
   }
 }
 
+// four consecutive values of an embedding row: one load where the caller's
+// table is aligned for it (vec), else one by one
+__device__ __forceinline__ float4 load4(const float* p, bool vec) {
+  return vec ? *reinterpret_cast<const float4*>(p) : make_float4(p[0], p[1], p[2], p[3]);
+}
+__device__ __forceinline__ float4 load4(const bf16* p, bool vec) {
+  if (!vec) return make_float4((float)p[0], (float)p[1], (float)p[2], (float)p[3]);
+  const bf16x4 v = *reinterpret_cast<const bf16x4*>(p);
+  return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+}
+
+// First kernel of a step, one block per recompute row n and then the blocks
+// of the rotary table:
+//   h[n] = E[mask ? mask_id : token] (fp32 residual; token ids outside
+//     [0, vocab) are read as [MASK]),
+//   out[n] = rmsnorm(h[n]) * g of the first layer (same sums as rmsnorm_kernel),
+//   cs[n][i] = (cos, sin) of pos(n) * theta^(-2i/head_dim), angle and trig in fp64.
+// Bound by its launch at few rows and by the scattered table rows at many:
+// separate embedding (one value per load and store), table and norm kernels
+// took 7.5 + 4.6 + 4.8 us at 32 rows of 4096 and 456 + 57 + 242 at 65536 rows
+// of 3584, this one 6.7 and 446. The table has blocks of its own because its
+// fp64 exponential and sine held up the rows' blocks (572 us with the table in
+// each row's last wave, 460 after its stores).
+template <typename T>
+__global__ __launch_bounds__(256) void embed_norm_kernel(
+    StepPlan p, const T* __restrict__ E, int d, int vocab, int mask_id,
+    const int32_t* __restrict__ tokens, const uint8_t* __restrict__ mask,
+    const float* __restrict__ g, float eps, int half, double log_theta, bool vec,
+    float* __restrict__ h, T* __restrict__ out, float2* __restrict__ cs) {
+  __shared__ float red[4];
+  if ((int)blockIdx.x >= p.n_rows) {        // table blocks: 256 / half rows each
+    const int per = 256 / half, base = ((int)blockIdx.x - p.n_rows) * per;
+    const int n = base + (int)threadIdx.x / half, i = threadIdx.x % half;
+    // a wave spans one or two rows: find each row's request by its own walk
+    const int row = min(n, p.n_rows - 1);
+    int r = plan_req_of_row(p, min(base, p.n_rows - 1));
+    while (r + 1 < p.n_req && p.r[r + 1].row0 <= row) ++r;
+    const double pos = (double)(p.r[r].pos0 + (row - p.r[r].row0));
+    const double freq = exp(-log_theta * (double)(2 * i) / (double)(2 * half));
+    double sn, cn;
+    sincos(pos * freq, &sn, &cn);
+    if (n < p.n_rows) cs[(long)n * half + i] = make_float2((float)cn, (float)sn);
+    return;
+  }
+  const int n = blockIdx.x;
+  const ReqPlan& q = p.r[plan_req_of_row(p, n)];
+  const int pos = q.pos0 + (n - q.row0);
+  const long ti = (long)q.tok_off + pos;
+  const int tk = tokens[ti];
+  const int id = (mask[ti] || tk < 0 || tk >= vocab) ? mask_id : tk;
+  const T* src = E + (long)id * d;
+  float* x = h + (long)n * d;
+  T* o = out + (long)n * d;
+  float ss = 0.f, inv;
+  if (d <= 4096) {                          // the row stays in registers
+    float4 v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int j = threadIdx.x * 4 + c * 1024;
+      if (j < d) v[c] = load4(src + j, vec);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int j = threadIdx.x * 4 + c * 1024;
+      if (j < d) {
+        *reinterpret_cast<float4*>(x + j) = v[c];
+        ss += v[c].x * v[c].x + v[c].y * v[c].y + v[c].z * v[c].z + v[c].w * v[c].w;
+      }
+    }
+    inv = 1.0f / sqrtf(block_sum_256(ss, red) / (float)d + eps);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int j = threadIdx.x * 4 + c * 1024;
+      if (j < d) {
+        const float4 gg = *reinterpret_cast<const float4*>(g + j);
+        store4(o + j, v[c].x * inv * gg.x, v[c].y * inv * gg.y, v[c].z * inv * gg.z,
+               v[c].w * inv * gg.w);
+      }
+    }
+  } else {
+    for (int j = threadIdx.x * 4; j < d; j += 1024) {
+      const float4 v = load4(src + j, vec);
+      *reinterpret_cast<float4*>(x + j) = v;
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+    inv = 1.0f / sqrtf(block_sum_256(ss, red) / (float)d + eps);
+    for (int j = threadIdx.x * 4; j < d; j += 1024) {
+      const float4 v = load4(src + j, vec);
+      const float4 gg = *reinterpret_cast<const float4*>(g + j);
+      store4(o + j, v.x * inv * gg.x, v.y * inv * gg.y, v.z * inv * gg.z, v.w * inv * gg.w);
+    }
+  }
+}
+
+template <typename T>
+hipError_t embed_norm_rows(const StepPlan& p, const T* E, int d, int vocab, int mask_id,
+                           const int32_t* tokens, const uint8_t* mask, const float* g, float eps,
+                           int head_dim, float theta, float* h, T* out, float2* cs,
+                           hipStream_t st) {
+  if (p.n_rows == 0) return hipSuccess;
+  const int per = 256 / (head_dim / 2);     // head_dim 64 or 128
+  DLM_LAUNCH(embed_norm_kernel<T>, dim3(p.n_rows + ceil_div(p.n_rows, per)), dim3(256), 0, st, p, E, d, vocab, mask_id,
+                     tokens, mask, g, eps, head_dim / 2, log((double)theta),
+             reinterpret_cast<uintptr_t>(E) % (4 * sizeof(T)) == 0, h, out, cs);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t add_rmsnorm_rows(float* h, const float* part, int splits, long stride, const float* g,
                             int n, int d, float eps, T* out, hipStream_t st) {
@@ -218,26 +297,6 @@ hipError_t final_norm_gather(const float* h, const float* g, const int* lm_rows,
 }
 
 // ----------------------------------------------------------------- RoPE --
-// cs[n][i] = (cos, sin) of pos(n) * theta^(-2i/dh), angle and trig in fp64.
-__global__ void rope_table_kernel(StepPlan p, int half, double log_theta, float2* cs) {
-  const int n = blockIdx.x;
-  const int r = plan_req_of_row(p, n);
-  const double pos = (double)(p.r[r].pos0 + (n - p.r[r].row0));
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const double freq = exp(-log_theta * (double)(2 * i) / (double)(2 * half));
-    double s, c;
-    sincos(pos * freq, &s, &c);
-    cs[(long)n * half + i] = make_float2((float)c, (float)s);
-  }
-}
-
-hipError_t rope_table(const StepPlan& p, int head_dim, float theta, float2* cs, hipStream_t st) {
-  if (p.n_rows == 0) return hipSuccess;
-  DLM_LAUNCH(rope_table_kernel, dim3(p.n_rows), dim3(64), 0, st, p, head_dim / 2,
-                     log((double)theta), cs);
-  return hipGetLastError();
-}
-
 // One block = one 64-row tile of one request x one head slot:
 //   y <  hq         : query head y   -> rotated, stored to q_out[n][y*dh..]
 //   y >= hq         : kv head y - hq -> rotated key to K[slot][j][pos][:],
@@ -391,32 +450,36 @@ hipError_t qkv_rope_scatter(const StepPlan& p, const float* qkv, int splits, lon
 // ----------------------------------------------------- LM row selection --
 // Rows that get a prediction: the masked positions of each active block
 // (all block positions when all_rows != 0), in request order, ascending
-// position. One wave per request counts with a ballot; a single block then
-// scans the counts in request order. Output indices are packed recompute rows.
+// position. One wave per request counts with a ballot; wave 0 then scans the
+// counts in request order. Output indices are packed recompute rows.
 __global__ __launch_bounds__(1024) void lm_select_kernel(StepPlan p, const uint8_t* __restrict__ mask,
                                                          int all_rows, int* __restrict__ lm_rows,
                                                          int* __restrict__ lm_count,
                                                          int* __restrict__ req_off,
                                                          int* __restrict__ req_cnt) {
   __shared__ unsigned long long bits[kMaxReq];
-  __shared__ int offs[kMaxReq + 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int r = wave; r < p.n_req; r += nw) {
-    const ReqPlan& q = p.r[r];
-    bool m = false;
-    if (lane < q.blk_len) m = all_rows || mask[(long)q.tok_off + q.blk_s + lane] != 0;
-    unsigned long long b = __ballot(m);
+  __shared__ int offs[kMaxReq];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = 16;   // 1024 threads
+#pragma unroll                              // the waves' mask loads in flight together
+  for (int u = 0; u < kMaxReq / 16; ++u) {
+    const int r = wave + 16 * u;
+    const ReqPlan& q = p.r[min(r, p.n_req - 1)];
+    const bool in = r < p.n_req && lane < q.blk_len;
+    const bool m = in && (all_rows || mask[(long)q.tok_off + q.blk_s + (in ? lane : 0)] != 0);
+    const unsigned long long b = __ballot(m);
     if (lane == 0) bits[r] = b;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int r = 0; r < p.n_req; ++r) {
-      offs[r] = acc;
-      acc += __popcll(bits[r]);
+  if (wave == 0) {                          // exclusive scan of the counts, one lane per request
+    const int cnt = lane < p.n_req ? __popcll(bits[lane]) : 0;
+    int incl = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
     }
-    offs[p.n_req] = acc;
-    *lm_count = acc;
+    offs[lane] = incl - cnt;
+    if (lane == 63) *lm_count = incl;
   }
   __syncthreads();
   for (int r = wave; r < p.n_req; r += nw) {
@@ -442,9 +505,15 @@ hipError_t lm_select_rows(const StepPlan& p, const uint8_t* mask, int all_rows, 
 }
 
 // --------------------------------------------------------- tile combine --
-// conf = 1 / S, tok = lowest argmax, from the per-vocab-tile statistics; one
-// wave per row, tiles strided over lanes, then a fixed xor tree: the result
-// does not depend on scheduling.
+// conf = 1 / S, tok = lowest argmax, from the per-vocab-tile statistics. One
+// block of 256 threads per R rows: thread t takes row t % R and the tiles
+// t / R, t / R + 256 / R, ..., four of them loaded before the first is used, then
+// a fixed tree over the row's threads: the result does not depend on
+// scheduling. The statistics of one tile are consecutive over the rows, so
+// R = 16 reads 64-byte runs (4096 rows x 594 tiles); R = 1 puts every thread
+// on one row where rows are few and the loads' latency is what counts (32 rows
+// x 988 tiles, one wave per row with one tile in flight: 15 us, now 7; 4096
+// rows x 594 tiles 23, now 14).
 struct Stat { float m; float s; int i; };
 __device__ __forceinline__ Stat comb(Stat a, Stat b) {
   Stat r;
@@ -456,37 +525,53 @@ __device__ __forceinline__ Stat comb(Stat a, Stat b) {
   return r;
 }
 
-__global__ void lm_combine_kernel(const float* __restrict__ pm, const float* __restrict__ ps,
-                                  const int* __restrict__ pi, int tiles, int ld,
-                                  const int* __restrict__ lm_count, float* __restrict__ conf,
-                                  int* __restrict__ tok) {
-  const int row = blockIdx.x;
-  if (row >= *lm_count) return;
-  const int lane = threadIdx.x;
-  Stat a = {-INFINITY, 0.f, 0x7fffffff};
-  for (int t = lane; t < tiles; t += 64) {
-    Stat b = {pm[(long)t * ld + row], ps[(long)t * ld + row], pi[(long)t * ld + row]};
-    a = comb(a, b);
-  }
+template <int R>
+__global__ __launch_bounds__(256) void lm_combine_kernel(
+    const float* __restrict__ pm, const float* __restrict__ ps, const int* __restrict__ pi,
+    int tiles, int ld, const int* __restrict__ lm_count, int m_max, float* __restrict__ conf,
+    int* __restrict__ tok) {
+  constexpr int G = 256 / R, UNR = 4;       // tile groups; tiles in flight per thread
+  __shared__ Stat part[256];
+  const int n = lm_count ? min(*lm_count, m_max) : m_max;
+  const int row0 = blockIdx.x * R;
+  if (row0 >= n) return;
+  const int row = min(row0 + (int)threadIdx.x % R, n - 1), grp = threadIdx.x / R;
+  const Stat none = {-INFINITY, 0.f, 0x7fffffff};
+  Stat a = none;
+  for (int t0 = grp; t0 < tiles; t0 += G * UNR) {
+    Stat b[UNR];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    Stat b;
-    b.m = __shfl_xor(a.m, o, 64);
-    b.s = __shfl_xor(a.s, o, 64);
-    b.i = __shfl_xor(a.i, o, 64);
-    a = comb(a, b);
+    for (int u = 0; u < UNR; ++u) {
+      const int t = t0 + u * G;
+      const long at = (long)t * ld + row;
+      b[u] = t < tiles ? Stat{pm[at], ps[at], pi[at]} : none;
+    }
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) a = comb(a, b[u]);
   }
-  if (lane == 0) {
-    conf[row] = 1.0f / a.s;
-    tok[row] = a.i;
+  part[threadIdx.x] = a;
+  for (int o = 128; o >= R; o >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < o) {
+      a = comb(a, part[threadIdx.x + o]);
+      part[threadIdx.x] = a;
+    }
+  }
+  if ((int)threadIdx.x < R && row0 + (int)threadIdx.x < n) {
+    conf[row0 + threadIdx.x] = 1.0f / a.s;
+    tok[row0 + threadIdx.x] = a.i;
   }
 }
 
 hipError_t lm_combine(const float* pm, const float* ps, const int* pi, int tiles, int ld,
                       const int* lm_count, int m_max, float* conf, int* tok, hipStream_t st) {
   if (m_max == 0) return hipSuccess;
-  DLM_LAUNCH(lm_combine_kernel, dim3(m_max), dim3(64), 0, st, pm, ps, pi, tiles, ld,
-                     lm_count, conf, tok);
+  if (m_max >= 1024)
+    DLM_LAUNCH(lm_combine_kernel<16>, dim3(ceil_div(m_max, 16)), dim3(256), 0, st, pm, ps, pi,
+                       tiles, ld, lm_count, m_max, conf, tok);
+  else
+    DLM_LAUNCH(lm_combine_kernel<1>, dim3(m_max), dim3(256), 0, st, pm, ps, pi, tiles, ld,
+                       lm_count, m_max, conf, tok);
   return hipGetLastError();
 }
 
@@ -639,8 +724,9 @@ hipError_t unmask_select(const StepPlan& p, const float* conf, const int* tok,
 }
 
 #define INST(T)                                                                                 \
-  template hipError_t embed_rows<T>(const StepPlan&, const T*, int, int, int, const int32_t*,  \
-                                    const uint8_t*, float*, hipStream_t);                      \
+  template hipError_t embed_norm_rows<T>(const StepPlan&, const T*, int, int, int,             \
+                                         const int32_t*, const uint8_t*, const float*, float,  \
+                                         int, float, float*, T*, float2*, hipStream_t);        \
   template hipError_t rmsnorm_rows<T>(const float*, const float*, int, int, float, T*,         \
                                       hipStream_t);                                            \
   template hipError_t add_rmsnorm_rows<T>(float*, const float*, int, long, const float*, int,  \

@@ -379,10 +379,9 @@ dlm_status run_forward(dlm_model* m, dlm_cache* c, const dlm_batch* b, const Ste
   float* part = reinterpret_cast<float*>(ws + L.part);
   T* act = reinterpret_cast<T*>(ws + L.act);
 
-  LAUNCH(m, st, "rope_table", rope_table(p, dh, cf.rope_theta, cs, st));
-  LAUNCH(m, st, "embed", embed_rows<T>(p, reinterpret_cast<const T*>(m->embed), d, cf.vocab, cf.mask_id,
-                         b->tokens, b->mask, h, st));
-  LAUNCH(m, st, "rmsnorm", rmsnorm_rows<T>(h, m->layers[0].attn_norm, n, d, cf.rms_eps, a, st));
+  LAUNCH(m, st, "embed_norm", embed_norm_rows<T>(p, reinterpret_cast<const T*>(m->embed), d, cf.vocab,
+                         cf.mask_id, b->tokens, b->mask, m->layers[0].attn_norm, cf.rms_eps, dh,
+                         cf.rope_theta, h, a, cs, st));
   const size_t es = sizeof(T);
   for (int l = 0; l < cf.n_layers; ++l) {
     const dlm_layer_weights& w = m->layers[l];
@@ -502,8 +501,6 @@ dlm_status check_handles(dlm_model* m, dlm_cache* c) {
   if (c->model != m) return fail(DLM_EINVAL, "cache was allocated for another model");
   return DLM_OK;
 }
-
-__global__ void fill_i32_kernel(int* p, int v) { *p = v; }
 
 }  // namespace
 
@@ -787,21 +784,18 @@ dlm_status dlm_head_confidence(dlm_model* m, const void* u_rows, int32_t m_rows,
   float* pm = reinterpret_cast<float*>(w);
   float* ps = reinterpret_cast<float*>(w + stat);
   int* pi = reinterpret_cast<int*>(w + 2 * stat);
-  int* cnt = reinterpret_cast<int*>(w + 3 * stat);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(1), 0, st, cnt, (int)m_rows);
-  HIPCHECK(hipGetLastError());
   const dlm_config& cf = m->cfg;
   if (cf.dtype == DLM_BF16) {
     HIPCHECK(gemm_lm_head<bf16>(gp, reinterpret_cast<const bf16*>(u_rows), cf.d_model,
                                 reinterpret_cast<const bf16*>(m->lm_head), m_rows, cf.vocab,
-                                cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, cnt, st));
+                                cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, nullptr, st));
   } else {
     HIPCHECK(gemm_lm_head<float>(gp, reinterpret_cast<const float*>(u_rows), cf.d_model,
                                  reinterpret_cast<const float*>(m->lm_head), m_rows, cf.vocab,
-                                 cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, cnt, st));
+                                 cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, nullptr, st));
   }
-  HIPCHECK(lm_combine(pm, ps, pi, tiles, m_rows, cnt, m_rows, conf, tok, st));
+  HIPCHECK(lm_combine(pm, ps, pi, tiles, m_rows, nullptr, m_rows, conf, tok, st));
   return DLM_OK;
 }
 
