@@ -3,14 +3,14 @@
 // sqrt(dh)) V per query head; query head h reads key/value head h / (Hq/Hkv).
 //
 // bf16 path (matrix cores), two kernels:
-//  * attn_gqa_kernel: one block = all query heads that share a key/value head
-//    (one for MHA) x 16-64 query rows of one request; 64-key tiles loaded
-//    directly into a two-stage LDS ring. Used for grouped-query attention and
-//    for MHA launches with at least two blocks per CU.
-//  * attn_bf16_kernel: one block = 32 or 64 query rows of one request x one
-//    query head; waves split the rows in groups of 16 and the keys in two
-//    groups, tiles staged through registers. Used for MHA launches with few
-//    blocks (one request's no-cache step, cache steps of short blocks).
+//  * attn_gqa_kernel (shared tiles): one block = eight (16 query rows, query
+//    head) groups that read one key/value head of one request; 64-key tiles
+//    loaded directly into a two-stage LDS ring. Used where it makes at least a
+//    block per CU.
+//  * attn_bf16_kernel (per head): one block = 32 or 64 query rows of one request
+//    x one query head; waves split the rows in groups of 16 and the keys in
+//    four or two groups, tiles staged through registers. Used for launches with
+//    few blocks (one request's no-cache step, cache steps of few requests).
 // Key tiles are staged in LDS keys row-major and values transposed, which is
 // how the cache stores them.
 // Each wave computes S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (keys as the A
@@ -316,10 +316,14 @@ __global__ __launch_bounds__(QG* KG * 64) void attn_bf16_kernel(StepPlan p, cons
   }
 }
 
-// Shared-tile kernel (GH query heads per key/value head; GH = 1 for MHA):
-// one block = the GH query heads of one key/value head x QG groups of 16
-// query rows of one request, one wave per (query head, row group), so every
-// staged K/V tile serves GH * QG * 16 query rows. Tiles of 64 keys are fetched with
+// Shared-tile kernel (gh query heads per key/value head; 1 for MHA): one block =
+// eight consecutive groups of (16 query rows, query head) that read one
+// key/value head of one request, one wave per group, heads fastest, so every
+// staged K/V tile serves 128 query rows whatever gh is (a launch of 7-head blocks
+// of seven waves left one SIMD in four with a wave less: 16 x 1024 rows of 28/4
+// heads 442 -> 375 us; MHA blocks of 64 rows moved each tile twice as often:
+// 8 x 1280 rows of 32 heads 443 -> 325 us). Waves whose group does not exist load
+// and meet the barriers only. Tiles of 64 keys are fetched with
 // direct global->LDS loads into a two-stage ring: the next tile's loads run
 // during the current tile's MFMAs and no registers hold tiles in flight,
 // which keeps the register count low enough for two blocks per CU.
@@ -339,16 +343,18 @@ __global__ __launch_bounds__(QG* KG * 64) void attn_bf16_kernel(StepPlan p, cons
 // Keys at or beyond L inside the last tile are read from the slot (a slot
 // holds s_max positions, a multiple of 64) and then masked: their scores are
 // set to -inf and their V^T entries cleared in LDS.
-template <int DH, int GH, int QG>
-__global__ __launch_bounds__(GH* QG * 64) void attn_gqa_kernel(StepPlan p, const bf16* __restrict__ q,
-                                                             const bf16* __restrict__ kc,
-                                                             const bf16* __restrict__ vc,
-                                                             int s_max, int hq, int hkv, int n_tiles,
-                                                             bf16* __restrict__ out,
-                                                             float scale_log2) {
-  constexpr int NW = GH * QG;              // waves
+constexpr int kSharedWaves = 8;
+// blocks of a request per key/value head
+__host__ __device__ constexpr int shared_blocks(int nrows, int gh) {
+  return ceil_div(ceil_div(nrows, 16) * gh, kSharedWaves);
+}
+template <int DH>
+__global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
+    StepPlan p, const bf16* __restrict__ q, const bf16* __restrict__ kc,
+    const bf16* __restrict__ vc, int s_max, int hq, int hkv, int n_tiles, bf16* __restrict__ out,
+    float scale_log2) {
+  constexpr int NW = kSharedWaves;
   constexpr int NT = NW * 64;
-  constexpr int QT = 16 * QG;              // query rows per block
   constexpr int SK = 64;                   // keys per tile
   constexpr int KRB = DH * 2;              // K row bytes
   constexpr int KCPR = DH / 8;             // 16-byte chunks per K row
@@ -377,21 +383,23 @@ __global__ __launch_bounds__(GH* QG * 64) void attn_gqa_kernel(StepPlan p, const
     tile = lid - kvh * n_tiles;
   }
   // request of this tile: tiles of QT rows are numbered request by request
+  const int gh = hq / hkv;
+  const int ln = threadIdx.x & 63;
   int t0;
-  const int r = plan_req_of_qtile(p, tile, QT, &t0);
+  const int r = plan_req_of_lane_tiles(p, tile, ln < p.n_req ? shared_blocks(p.r[ln].nrows, gh) : 0, &t0);
   const ReqPlan& rq = p.r[r];
-  const int lrow0 = (tile - t0) * QT;
-  const int nvalid = min(QT, rq.nrows - lrow0);
   const int L = rq.seq_len;
   const bf16* kb = kc + ((long)(rq.slot * hkv + kvh) * s_max) * DH;
   const bf16* vb = vc + ((long)(rq.slot * hkv + kvh) * DH) * s_max;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int qg = wave % QG;                       // 16-row group
-  const int h = kvh * GH + wave / QG;             // query head
-  const int qr = qg * 16 + (lane & 15);           // query row of this lane in the tile
-  const bool q_ok = qr < nvalid;
-  const long qrow = rq.row0 + lrow0 + qr;
+  const int grp = (tile - t0) * NW + wave;        // this wave's (row group, head)
+  const int row16 = grp / gh * 16;
+  const int h = kvh * gh + grp % gh;              // query head
+  const int qr = row16 + (lane & 15);             // query row of this lane in the request
+  const bool q_ok = qr < rq.nrows;
+  const bool w_ok = row16 < rq.nrows;             // uniform over the wave
+  const long qrow = rq.row0 + qr;
   const int g = lane >> 4;
 
   // this wave's load instructions: j = wave + NW m over the tile's NI
@@ -470,6 +478,7 @@ __global__ __launch_bounds__(GH* QG * 64) void attn_gqa_kernel(StepPlan p, const
       __syncthreads();
     }
     if (t + 1 < ntiles) issue((t + 1) & 1, key0 + SK);
+    if (!w_ok) continue;                          // no rows: load and meet the barriers only
 
     // S^T blocks: sblk[kb][i] = raw score(key = key0 + pi(16 kb + 4 g + i), query = lane & 15)
     f32x4 sblk[4];
@@ -683,47 +692,52 @@ static hipError_t launch_attn(const StepPlan& p, const bf16* q, const bf16* kc, 
   return hipGetLastError();
 }
 
-template <int DH, int GH, int QG>
+template <int DH>
 static hipError_t launch_gqa(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
                              int s_max, int hq, int hkv, bf16* out, float scale_log2,
                              hipStream_t st) {
-  constexpr int QT = 16 * QG;
   int tiles = 0;
-  for (int r = 0; r < p.n_req; ++r) tiles += (p.r[r].nrows + QT - 1) / QT;
+  for (int r = 0; r < p.n_req; ++r) tiles += shared_blocks(p.r[r].nrows, hq / hkv);
   if (tiles == 0) return hipSuccess;
-  DLM_LAUNCH((attn_gqa_kernel<DH, GH, QG>), dim3(hkv * tiles), dim3(GH * QG * 64), 0,
-                     st, p, q, kc, vc, s_max, hq, hkv, tiles, out, scale_log2);
+  DLM_LAUNCH((attn_gqa_kernel<DH>), dim3(hkv * tiles), dim3(kSharedWaves * 64), 0, st, p, q, kc,
+             vc, s_max, hq, hkv, tiles, out, scale_log2);
   return hipGetLastError();
 }
 
-// Grouped-query attention with 2, 4, 7 or 8 query heads per key/value head:
-// the shared-tile kernel with 7 or 8 waves per block.
+// Which kernel (times are one layer's launch on MI355X, 256 CUs, head_dim 128,
+// chosen kernel against the other):
+//  * The shared-tile kernel with at least 256 blocks (28/4 heads, 16 x 64 rows
+//    over 1024 keys: 38 us against 51; 32 heads, 1476 rows 74 / 97, 8 x 128 rows
+//    over 1152 keys 41 / 56). With fewer, CUs idle behind a serial key walk
+//    (28/4 heads, 3 x 64 rows over 2300 keys 35 / 69, 8 x 64 over 1024 27 / 35; 32
+//    heads, 512 rows 16 / 20). Where no request has more than 32 rows its
+//    blocks compute in two waves of eight and are read-bound: 512 blocks (32 heads,
+//    8 x 32 rows over 1280 keys 36.6 / 37.7, 16 x 32 71.1 / 69.8), and over short
+//    sequences its loads by all eight waves win at any count (32 rows over 200 keys
+//    10.4 / 12.3, over 517 16.9 / 18.5, over 2300 47.6 / 39.9).
+//  * Otherwise the per-head kernel: 32 query rows and four key groups (8 waves)
+//    while that is at most one block per CU or no request has more than 32 rows
+//    (32 rows over 2300 keys 40 us, with two key groups 45), else 64 rows and two
+//    key groups (512 rows 16.4 us, with 32-row blocks 23).
 template <int DH>
 static hipError_t attention_dh(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
                                int s_max, int hq, int hkv, bf16* out, float scale_log2,
                                hipStream_t st) {
-  switch (hkv > 0 && hq % hkv == 0 ? hq / hkv : 0) {
-    case 2: return launch_gqa<DH, 2, 4>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-    case 4: return launch_gqa<DH, 4, 2>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-    case 7: return launch_gqa<DH, 7, 1>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-    case 8: return launch_gqa<DH, 8, 1>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-    default: break;
-  }
-  // MHA and other ratios. With at least two 64-row blocks per CU (256 CUs)
-  // the shared-tile kernel with one head per block (4 waves) is used: its
-  // blocks overlap each other's loads. Otherwise the per-head kernel with
-  // two key groups per block (8 waves), on query tiles of 32 rows when no
-  // request recomputes more than 32 rows (cache steps of blocks <= 32), else
-  // 64.
-  int max_rows = 0, tiles64 = 0;
+  if (hkv < 1 || hq % hkv != 0) return hipErrorInvalidValue;
+  int max_rows = 0, max_len = 0;
+  long shared = 0, t32 = 0;
   for (int r = 0; r < p.n_req; ++r) {
-    max_rows = max(max_rows, p.r[r].nrows);
-    tiles64 += (p.r[r].nrows + 63) / 64;
+    const int n = p.r[r].nrows;
+    max_rows = max(max_rows, n);
+    max_len = max(max_len, p.r[r].seq_len);
+    shared += (long)hkv * shared_blocks(n, hq / hkv);
+    t32 += ceil_div(n, 32);
   }
-  if (hq == hkv && max_rows > 32 && (long)hq * tiles64 >= 512)
-    return launch_gqa<DH, 1, 4>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-  return max_rows <= 32
-             ? launch_attn<DH, 2, 2>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st)
+  const bool few = max_rows <= 32, brief = few && max_len <= 640 && hq == hkv && DH == 128;
+  if (brief || shared >= (few ? 512 : 256))
+    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
+  return few || hq * t32 <= 256
+             ? launch_attn<DH, 2, 4>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st)
              : launch_attn<DH, 4, 2>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
 }
 

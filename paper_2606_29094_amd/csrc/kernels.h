@@ -49,9 +49,9 @@ __device__ __forceinline__ int plan_req_of_tile(const StepPlan& p, int tile) {
   const int lane = threadIdx.x & 63;
   return __popcll(__ballot(lane < p.n_req && p.r[lane].tile0 <= tile)) - 1;
 }
-__device__ __forceinline__ int plan_req_of_qtile(const StepPlan& p, int tile, int qt, int* t0) {
+// nt: tiles of this lane's request (any numbering of tiles request by request)
+__device__ __forceinline__ int plan_req_of_lane_tiles(const StepPlan& p, int tile, int nt, int* t0) {
   const int lane = threadIdx.x & 63;
-  const int nt = lane < p.n_req ? (p.r[lane].nrows + qt - 1) / qt : 0;
   int incl = nt;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
@@ -61,6 +61,11 @@ __device__ __forceinline__ int plan_req_of_qtile(const StepPlan& p, int tile, in
   const int r = __popcll(__ballot(lane < p.n_req && incl <= tile));
   *t0 = __builtin_amdgcn_readlane(incl - nt, r);
   return r;
+}
+__device__ __forceinline__ int plan_req_of_qtile(const StepPlan& p, int tile, int qt, int* t0) {
+  const int lane = threadIdx.x & 63;
+  const int nt = lane < p.n_req ? (p.r[lane].nrows + qt - 1) / qt : 0;
+  return plan_req_of_lane_tiles(p, tile, nt, t0);
 }
 
 // ---- GEMM family (gemm.hip, gemm_dl.hip) ----

@@ -1,0 +1,85 @@
+"""GPU checks of the bf16 attention kernels at the edges of their dispatch and of
+their tiles, on exactly the values each launch received (dlm_debug_trace),
+against fp64 softmax attention over the slot's cached keys and values. The cache
+holds NaN wherever no step wrote, so a read past a sequence that reaches the
+result shows."""
+import numpy as np
+import pytest
+import torch
+
+from kernel_checks import U, half_ulp
+from paper_2606_29094_amd import engine
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(gpu, hq, hkv, dh, seed):
+    d, V, ffn = 128, 65, 64
+    g = torch.Generator().manual_seed(seed)
+    mat = lambda r, c, s=0.1: (torch.randn(r, c, generator=g) * s).to(torch.bfloat16).to(gpu)
+    one = lambda: torch.ones(d, device=gpu)
+    t = {"embed": mat(V, d, 1.0), "lm_head": mat(V, d), "final_norm": one(),
+         "layers": [{"attn_norm": one(), "w_qkv": mat((hq + 2 * hkv) * dh, d), "w_o": mat(d, hq * dh),
+                     "ffn_norm": one(), "w_gate_up": mat(2 * ffn, d), "w_down": mat(d, ffn)}]}
+    return engine.DeviceModel(engine.ModelShape(1, d, hq, hkv, dh, ffn, V, "bf16"), t, 1.0)
+
+
+# (query heads, key/value heads, head_dim, prompt lengths, gen, block, mode, step kind)
+CASES = [
+    # shared tiles, blocks of eight (row group, head) pairs: ratio 1, 3, 7; rows of one
+    # to seventeen groups, a last group of one row, a partly filled last block
+    (32, 32, 128, [255, 1, 600, 17, 64], 64, 32, "none", "refresh"),
+    (12, 4, 64, [1000, 513, 3], 40, 40, "none", "refresh"),
+    (28, 4, 128, [1100, 33], 64, 64, "none", "refresh"),
+    # shared tiles over short sequences, one block of 32 rows per head
+    (32, 32, 128, [200], 64, 32, "dual", "cache"),
+    (8, 8, 128, [1, 576], 64, 31, "dual", "cache"),
+    # per head, 32 rows and four key groups: fewer keys than groups, several turns
+    (4, 4, 64, [5], 9, 9, "dual", "cache"),
+    (8, 8, 128, [900, 641], 64, 32, "dual", "cache"),
+    (28, 4, 128, [400, 20, 130], 200, 64, "dual", "cache"),
+    # per head, 64 rows and two key groups (more than 256 blocks of 32 rows)
+    (32, 32, 128, [256], 256, 32, "none", "refresh"),
+    # cache and recompute requests in one launch
+    (32, 32, 128, [300, 40, 700, 128, 90, 511], 64, 32, "dual", "mixed"),
+    (28, 4, 64, [300, 40, 700, 128], 64, 64, "dual", "mixed"),
+]
+
+
+@pytest.mark.parametrize("hq,hkv,dh,prompts,gen,block,mode,kind", CASES)
+def test_attention_matches_fp64_on_its_inputs(gpu, hq, hkv, dh, prompts, gen, block, mode, kind):
+    model = _model(gpu, hq, hkv, dh, seed=sum(prompts))
+    eng = engine.Engine(model, len(prompts), max(prompts) + gen, mode)
+    eng.cache_buf.view(torch.bfloat16).fill_(float("nan"))
+    rng = np.random.default_rng(2)
+    reqs = []
+    for p in prompts:
+        r = engine.Request(rng.integers(0, 64, p).astype(np.int32), gen, block, 0.9)
+        eng.admit(r, 64)
+        reqs.append(r)
+    if kind != "refresh":
+        eng.refresh(reqs)
+        if kind == "mixed":
+            reqs[0].refreshed_block = reqs[-1].refreshed_block = -1
+    rows = eng.step_rows(reqs)
+    buf, _ = eng.debug_trace(reqs, 0, logits=False)
+    torch.cuda.synchronize()
+    base = 0
+    for r, (r0, r1) in zip(reqs, rows):
+        n, L = r1 - r0, r.seq_len
+        k, v = (x.double().numpy() for x in eng.read_kv(0, r.slot, L))
+        q = buf["q"][base:base + n].double().cpu().numpy().reshape(n, hq, dh)
+        got = buf["attn_out"][base:base + n].double().cpu().numpy().reshape(n, hq, dh)
+        assert np.isfinite(got).all()
+        for h in range(hq):
+            kh, vh = k[:, h // (hq // hkv)], v[:, h // (hq // hkv)]
+            s = q[:, h] @ kh.T / np.sqrt(dh)
+            w = np.exp(s - s.max(1, keepdims=True))
+            o = (w / w.sum(1, keepdims=True)) @ vh
+            # two-term bf16 P and fp32 sums (as kernel_checks), the fp32 error of
+            # the scores through the exponential, then the bf16 store
+            mag = (np.abs(q[:, h]) @ np.abs(kh).T / np.sqrt(dh)).max()
+            slack = (2.0 ** -15 + (L / 16 + 16 + 2 * dh / 32 * mag) * U) * np.abs(vh).max()
+            err = half_ulp(np.abs(o) + slack, "bf16") + slack
+            assert np.all(np.abs(got[:, h] - o) <= err), (r0, n, L, h)
+        base += n
