@@ -406,6 +406,8 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   auto slice_us = [&](int s) {
     return s > 1 ? (double)M * N * 4.0 * (s - 1) / (M <= few_rows ? 8.0e12 : 5.0e12) * 1e6 : 0.0;
   };
+  long best_units = 0;
+  const bool streams = (double)N * K * es > 256e6;   // weights larger than the last-level cache
   double best_t = 1e30;
   if (M <= few_rows) {
     for (const FewRowTable& c : kFewRowTables) {
@@ -423,8 +425,19 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
         if (t < best_t * 0.999) {
           best_t = t;
           best = GemmPlan{c.cfg, s, 0};
+          best_units = units;
         }
       }
+    }
+    // Streaming weights in several rounds of which the last is not nearly full: the
+    // tables below, which split the last round of large tiles (GQA gate/up 37888x3584:
+    // 384 rows 131 -> 125 us, 512 136 -> 132, 560 170 -> 156, 960 253 -> 224; 300
+    // rows, two rounds to 0.93, stay: 95.7 us against 118.6). Weights that fit the
+    // cache stay too (MHA gate/up 24576x4096, 560 rows, 1.5 rounds: 115 against 138).
+    const long rem = best_units % num_cu;
+    if (streams && best_units > num_cu && rem != 0 && rem < 0.8 * num_cu) {
+      few_rows = 0;
+      best_t = 1e30;
     }
   }
   for (const RoundTable& c : kRoundTables) {
@@ -469,7 +482,7 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   // from HBM once per row tile in plain order: use the grouped XCD order
   int bm, bn, th;
   if (best.cfg >= 0 && gemm_dl_tile(best.cfg, &bm, &bn, &th) && ceil_div(M, bm) > 1 &&
-      (double)N * K * es > 256e6)
+      streams)
     best.group_m = 8;
   return best;
 }
