@@ -6,11 +6,12 @@
 //  * attn_gqa_kernel (shared tiles): one block = eight (16 query rows, query
 //    head) groups that read one key/value head of one request; 64-key tiles
 //    loaded directly into a two-stage LDS ring. Used where it makes at least a
-//    block per CU.
+//    block per CU, and for few blocks over long sequences with the keys split
+//    over blocks, whose partials attn_merge_kernel adds.
 //  * attn_bf16_kernel (per head): one block = 32 or 64 query rows of one request
 //    x one query head; waves split the rows in groups of 16 and the keys in
 //    four or two groups, tiles staged through registers. Used for launches with
-//    few blocks (one request's no-cache step, cache steps of few requests).
+//    few blocks that a key split does not pay for (one request's no-cache step).
 // Key tiles are staged in LDS keys row-major and values transposed, which is
 // how the cache stores them.
 // Each wave computes S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (keys as the A
@@ -24,6 +25,8 @@
 //
 // fp32 path: attn_f32_kernel, on v_mfma_f32_16x16x4_f32; it serves the small
 // fp32 model.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -348,11 +351,14 @@ constexpr int kSharedWaves = 8;
 __host__ __device__ constexpr int shared_blocks(int nrows, int gh) {
   return ceil_div(ceil_div(nrows, 16) * gh, kSharedWaves);
 }
-template <int DH>
+// SPLIT: blockIdx also counts the key splits, each a contiguous range of the
+// request's key tiles; a block leaves its unnormalised O and (m, l) of every
+// (row, head) in po and ml, [split][row][head], for attn_merge_kernel.
+template <int DH, bool SPLIT>
 __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
     StepPlan p, const bf16* __restrict__ q, const bf16* __restrict__ kc,
     const bf16* __restrict__ vc, int s_max, int hq, int hkv, int n_tiles, bf16* __restrict__ out,
-    float scale_log2) {
+    float scale_log2, int splits, float* __restrict__ po, float2* __restrict__ ml) {
   constexpr int NW = kSharedWaves;
   constexpr int NT = NW * 64;
   constexpr int SK = 64;                   // keys per tile
@@ -374,13 +380,19 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
   // range of (key/value head, query tile) with query tiles fastest, so the
   // row tiles of one request and key/value head run on one XCD at about the
   // same time and share its L2.
-  int kvh, tile;
+  int kvh, tile, split = 0;
   {
     const int total = gridDim.x, id = blockIdx.x;
     const int xcd = id % kXcds, per = total / kXcds, rem = total % kXcds;
     const int lid = xcd * per + min(xcd, rem) + id / kXcds;
-    kvh = lid / n_tiles;
-    tile = lid - kvh * n_tiles;
+    const int row = lid / n_tiles;                // (key/value head, split)
+    tile = lid - row * n_tiles;
+    if constexpr (SPLIT) {
+      kvh = row / splits;
+      split = row - kvh * splits;
+    } else {
+      kvh = row;
+    }
   }
   // request of this tile: tiles of QT rows are numbered request by request
   const int gh = hq / hkv;
@@ -450,9 +462,14 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
   float m_ref = -INFINITY, l_run = 0.f;
   const int sw = (lane & 7) << 4;                 // chunk-slot XOR of rows 16 b + (lane & 15)
 
-  const int ntiles = ceil_div(L, SK);
-  issue(0, 0);
-  for (int t = 0; t < ntiles; ++t) {
+  int tbeg = 0, ntiles = ceil_div(L, SK);         // this block's key tiles [tbeg, ntiles)
+  if constexpr (SPLIT) {
+    const int per = ceil_div(ntiles, splits);
+    tbeg = split * per;
+    ntiles = min(ntiles, tbeg + per);
+  }
+  if (!SPLIT || tbeg < ntiles) issue(tbeg & 1, tbeg * SK);
+  for (int t = tbeg; t < ntiles; ++t) {
     const int key0 = t * SK;
     wait_vmcnt<0>();
     __syncthreads();                              // tile t in LDS; stage (t + 1) & 1 free
@@ -547,6 +564,16 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
   // finish: l over the 4 lanes sharing the query, normalise, store
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
+  if constexpr (SPLIT) {                          // no tiles: (-inf, 0) and zeros
+    if (q_ok) {
+      const long at = ((long)split * p.n_rows + qrow) * hq + h;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        *reinterpret_cast<f32x4*>(po + at * DH + db * 16 + 4 * g) = o[db];
+      if (g == 0) ml[at] = make_float2(m_ref, l_run);
+    }
+    return;
+  }
   const float inv = 1.0f / l_run;
   if (q_ok) {
     bf16* dstp = out + qrow * hq * DH + h * DH;
@@ -558,6 +585,52 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
       *reinterpret_cast<bf16x4*>(dstp + db * 16 + 4 * g) = v;
     }
   }
+}
+
+// Adds the key splits of each (row, head): DH / 4 lanes per item, the splits'
+// loads in flight together, sums in split order.
+constexpr int kMaxSplits = 8;   // more measured no faster
+template <int DH>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ po,
+                                                         const float2* __restrict__ ml, int items,
+                                                         int splits, bf16* __restrict__ out,
+                                                         float scale_log2) {
+  constexpr int LPI = DH / 4;              // lanes per item
+  const int item = blockIdx.x * (256 / LPI) + threadIdx.x / LPI, c = threadIdx.x % LPI * 4;
+  if (item >= items) return;
+  float mm = -INFINITY, l = 0.f;
+  f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < splits; s0 += 4) {
+    float2 x[4];
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const long at = (long)min(s0 + u, splits - 1) * items + item;
+      x[u] = ml[at];
+      v[u] = *reinterpret_cast<const f32x4*>(po + at * DH + c);
+    }
+    float mn = mm;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) mn = fmaxf(mn, x[u].x);
+    if (mn != mm) {                        // (mm = -inf: nothing added yet)
+      const float a = __builtin_amdgcn_exp2f((mm - mn) * scale_log2);
+      l *= a;
+      o *= a;
+      mm = mn;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (s0 + u >= splits || x[u].y == 0.f) continue;   // l = 0: the split has no keys
+      const float a = __builtin_amdgcn_exp2f((x[u].x - mm) * scale_log2);
+      l += x[u].y * a;
+      o += v[u] * a;
+    }
+  }
+  const float inv = 1.0f / l;
+  bf16x4 r;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r[i] = (bf16)(o[i] * inv);
+  *reinterpret_cast<bf16x4*>(out + (long)item * DH + c) = r;
 }
 
 // fp32 (the small fp32 model): one block = 16 query rows of one request x one
@@ -694,66 +767,133 @@ static hipError_t launch_attn(const StepPlan& p, const bf16* q, const bf16* kc, 
 
 template <int DH>
 static hipError_t launch_gqa(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                             int s_max, int hq, int hkv, bf16* out, float scale_log2,
-                             hipStream_t st) {
+                             int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
+                             float* scratch, hipStream_t st) {
   int tiles = 0;
   for (int r = 0; r < p.n_req; ++r) tiles += shared_blocks(p.r[r].nrows, hq / hkv);
   if (tiles == 0) return hipSuccess;
-  DLM_LAUNCH((attn_gqa_kernel<DH>), dim3(hkv * tiles), dim3(kSharedWaves * 64), 0, st, p, q, kc,
-             vc, s_max, hq, hkv, tiles, out, scale_log2);
+  if (splits == 1)
+    DLM_LAUNCH((attn_gqa_kernel<DH, false>), dim3(hkv * tiles), dim3(kSharedWaves * 64), 0, st, p,
+               q, kc, vc, s_max, hq, hkv, tiles, out, scale_log2, 1, nullptr, nullptr);
+  else
+    DLM_LAUNCH((attn_gqa_kernel<DH, true>), dim3(hkv * tiles * splits), dim3(kSharedWaves * 64), 0,
+               st, p, q, kc, vc, s_max, hq, hkv, tiles, out, scale_log2, splits, scratch,
+               reinterpret_cast<float2*>(scratch + (size_t)splits * p.n_rows * hq * DH));
   return hipGetLastError();
 }
 
-// Which kernel (times are one layer's launch on MI355X, 256 CUs, head_dim 128,
+// Which kernel where attention_splits leaves the keys whole (times are one layer's launch on MI355X, 256 CUs, head_dim 128,
 // chosen kernel against the other):
 //  * The shared-tile kernel with at least 256 blocks (28/4 heads, 16 x 64 rows
 //    over 1024 keys: 38 us against 51; 32 heads, 1476 rows 74 / 97, 8 x 128 rows
-//    over 1152 keys 41 / 56). With fewer, CUs idle behind a serial key walk
+//    over 1152 keys 41 / 56), or where the per-head kernel's 64-row blocks pass one
+//    per CU and a second round of them starts (32 heads, 560 rows 21.8 / 32.7, 960
+//    33.4 / 46.7; 28/4 heads, 600 rows 22.5 / 33.3, 1100 38.8 / 52.9). With
+//    fewer, CUs idle behind a serial key walk
 //    (28/4 heads, 3 x 64 rows over 2300 keys 35 / 69, 8 x 64 over 1024 27 / 35; 32
 //    heads, 512 rows 16 / 20). Where no request has more than 32 rows its
 //    blocks compute in two waves of eight and are read-bound: 512 blocks (32 heads,
 //    8 x 32 rows over 1280 keys 36.6 / 37.7, 16 x 32 71.1 / 69.8), and over short
 //    sequences its loads by all eight waves win at any count (32 rows over 200 keys
-//    10.4 / 12.3, over 517 16.9 / 18.5, over 2300 47.6 / 39.9).
+//    10.4 / 12.3, over 517 16.9 / 18.5, over 2300 47.6 / 39.9); over up to three key
+//    tiles, less than one of the per-head kernel's four-group turns, they do for any
+//    rows and heads (32 heads, 64 rows over 64 keys 5.5 / 10.9, 192 over 192 9.8 / 10.5;
+//    28/4 heads 7.0 / 10.6, 10.3 / 11.0).
 //  * Otherwise the per-head kernel: 32 query rows and four key groups (8 waves)
 //    while that is at most one block per CU or no request has more than 32 rows
 //    (32 rows over 2300 keys 40 us, with two key groups 45), else 64 rows and two
 //    key groups (512 rows 16.4 us, with 32-row blocks 23).
 template <int DH>
 static hipError_t attention_dh(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                               int s_max, int hq, int hkv, bf16* out, float scale_log2,
-                               hipStream_t st) {
-  if (hkv < 1 || hq % hkv != 0) return hipErrorInvalidValue;
+                               int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
+                               float* scratch, hipStream_t st) {
+  if (hkv < 1 || hq % hkv != 0 || splits < 1 || splits > kMaxSplits) return hipErrorInvalidValue;
+  if (splits > 1)
+    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
   int max_rows = 0, max_len = 0;
-  long shared = 0, t32 = 0;
+  long shared = 0, t32 = 0, t64 = 0;
   for (int r = 0; r < p.n_req; ++r) {
     const int n = p.r[r].nrows;
     max_rows = max(max_rows, n);
     max_len = max(max_len, p.r[r].seq_len);
     shared += (long)hkv * shared_blocks(n, hq / hkv);
     t32 += ceil_div(n, 32);
+    t64 += ceil_div(n, 64);
   }
-  const bool few = max_rows <= 32, brief = few && max_len <= 640 && hq == hkv && DH == 128;
-  if (brief || shared >= (few ? 512 : 256))
-    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
+  const bool few = max_rows <= 32;
+  const bool brief = DH == 128 && (max_len <= 192 || (few && max_len <= 640 && hq == hkv));
+  if (brief || shared >= (few ? 512 : 256) || (!few && hq * t64 > 256))
+    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, 1, nullptr, st);
   return few || hq * t32 <= 256
              ? launch_attn<DH, 2, 4>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st)
              : launch_attn<DH, 4, 2>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
 }
 
+// Key splits of the shared-tile kernel, so that a launch of few blocks fills
+// the CUs instead of walking all keys in each. As many as make about a block per
+// CU (288: 96 blocks take 3 splits), where the longest walk gets shorter by enough key
+// tiles, about 1 us each, to pay for the merge launch (4 us, and the partials' way
+// through memory: a tile per 16384 (row, head, split)). One layer's launch and merge
+// against the unsplit kernel chosen below, MI355X, head_dim 128:
+//   32 heads: 32 rows over 517 keys 6.8 + 4.0 us against 15.5, over 2300 14.7 + 4.1
+//     / 42, 2 x 57 rows over 1200 13.5 + 4.1 / 28, 4 x 32 over 1280 22.2 + 4.1 / 28.1
+//   28/4 heads: 64 rows over 900 keys 8.0 + 4.0 / 21.6, 4 x 57 over 2300 26.0 + 4.1
+//     / 46.5, 8 x 32 over 600 13.8 + 4.3 / 22.6, 8 x 64 over 1024 22.4 + 4.4 / 28.0
+//   left unsplit: 32 heads, 32 rows over 200 keys 6.3 + 4.1 / 9.1, 200 rows over 200
+//     9.8 + 4.3 / 11.4, 512 rows over 512 15.1 + 4.6 / 16.0, 8 x 32 over 1280 36.6 + 4.3
+//     / 37.8; 28/4 heads, 512 rows over 512 15.3 + 4.4 / 15.5
+int attention_splits(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
+                     size_t scratch_bytes) {
+  if (elem != 2 || hkv < 1 || hq % hkv != 0) return 1;
+  int max_len = 0;
+  long blocks = 0;
+  for (int r = 0; r < p.n_req; ++r) {
+    max_len = max(max_len, p.r[r].seq_len);
+    blocks += (long)hkv * shared_blocks(p.r[r].nrows, hq / hkv);
+  }
+  if (blocks == 0) return 1;
+  const size_t one = (size_t)p.n_rows * hq * (dh * sizeof(float) + sizeof(float2));
+  const long room = (long)std::min((size_t)kMaxSplits, scratch_bytes / one);
+  const int s = (int)std::min(288 / blocks, room);
+  if (s < 2) return 1;
+  const int nt = ceil_div(max_len, 64), per = ceil_div(nt, s);
+  if (nt - per < 5 + (long)p.n_rows * hq * s / 16384) return 1;
+  return ceil_div(nt, per);
+}
+
+hipError_t attention_merge(const StepPlan& p, int hq, int dh, int splits, const float* scratch,
+                           bf16* out, hipStream_t st) {
+  const int items = p.n_rows * hq;
+  if (items == 0) return hipSuccess;
+  const float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
+  const float2* ml = reinterpret_cast<const float2*>(scratch + (size_t)splits * items * dh);
+  if (dh == 128)
+    DLM_LAUNCH(attn_merge_kernel<128>, dim3(ceil_div(items, 8)), dim3(256), 0, st, scratch, ml,
+               items, splits, out, scale_log2);
+  else if (dh == 64)
+    DLM_LAUNCH(attn_merge_kernel<64>, dim3(ceil_div(items, 16)), dim3(256), 0, st, scratch, ml,
+               items, splits, out, scale_log2);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 template <>
 hipError_t attention<bf16>(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                           int s_max, int hq, int hkv, int dh, bf16* out, hipStream_t st) {
+                           int s_max, int hq, int hkv, int dh, bf16* out, int splits,
+                           float* scratch, hipStream_t st) {
   if (p.n_rows == 0) return hipSuccess;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
-  if (dh == 128) return attention_dh<128>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
-  if (dh == 64) return attention_dh<64>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
+  if (dh == 128) return attention_dh<128>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
+  if (dh == 64) return attention_dh<64>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
   return hipErrorInvalidValue;
 }
 
 template <>
 hipError_t attention<float>(const StepPlan& p, const float* q, const float* kc, const float* vc,
-                            int s_max, int hq, int hkv, int dh, float* out, hipStream_t st) {
+                            int s_max, int hq, int hkv, int dh, float* out, int splits, float*,
+                            hipStream_t st) {
+  if (splits != 1) return hipErrorInvalidValue;
   if (p.n_tiles == 0) return hipSuccess;
   const float scale = 1.0f / sqrtf((float)dh);
   int tiles = 0;

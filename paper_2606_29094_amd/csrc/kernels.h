@@ -168,8 +168,17 @@ hipError_t unmask_select(const StepPlan& p, const float* conf, const int* tok,
                          float* stats, hipStream_t st);
 
 // ---- attention (attention.hip) ----
+// splits > 1 (bf16): every block takes one of that many key ranges and leaves its
+// partial in scratch; attention_merge then writes out. splits comes from
+// attention_splits for the step's plan, which keeps the partials within
+// scratch_bytes (16-byte aligned; 1: scratch is not used).
+int attention_splits(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
+                     size_t scratch_bytes);
 template <typename T>
 hipError_t attention(const StepPlan& p, const T* q, const T* kcache, const T* vcache,
-                     int s_max, int hq, int hkv, int dh, T* out, hipStream_t st);
+                     int s_max, int hq, int hkv, int dh, T* out, int splits, float* scratch,
+                     hipStream_t st);
+hipError_t attention_merge(const StepPlan& p, int hq, int dh, int splits, const float* scratch,
+                           bf16* out, hipStream_t st);
 
 }  // namespace dlm

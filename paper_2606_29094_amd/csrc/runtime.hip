@@ -378,6 +378,8 @@ dlm_status run_forward(dlm_model* m, dlm_cache* c, const dlm_batch* b, const Ste
   T* ao = reinterpret_cast<T*>(ws + L.ao);
   float* part = reinterpret_cast<float*>(ws + L.part);
   T* act = reinterpret_cast<T*>(ws + L.act);
+  // part and act (consecutive) hold nothing while attention runs: its key splits' partials go there
+  const int ksplit = attention_splits(p, hq, hkv, dh, sizeof(T), L.lm_rows - L.part);
 
   LAUNCH(m, st, "embed_norm", embed_norm_rows<T>(p, reinterpret_cast<const T*>(m->embed), d, cf.vocab,
                          cf.mask_id, b->tokens, b->mask, m->layers[0].attn_norm, cf.rms_eps, dh,
@@ -398,7 +400,10 @@ dlm_status run_forward(dlm_model* m, dlm_cache* c, const dlm_batch* b, const Ste
     LAUNCH(m, st, "rope_kv_write", qkv_rope_scatter<T>(p, qkv, L.s_qkv, (long)n * qkv_dim, cs, hq, hkv, dh, q, kc, vc,
                                  c->s_max, st));
     if (t) TRACE_COPY(t->q, q, (size_t)n * qd * es);
-    LAUNCH(m, st, "attention", attention<T>(p, q, kc, vc, c->s_max, hq, hkv, dh, ao, st));
+    LAUNCH(m, st, "attention", attention<T>(p, q, kc, vc, c->s_max, hq, hkv, dh, ao, ksplit, part, st));
+    if constexpr (sizeof(T) == 2)
+      if (ksplit > 1)
+        LAUNCH(m, st, "attention_merge", attention_merge(p, hq, dh, ksplit, part, ao, st));
     if (t) TRACE_COPY(t->attn_out, ao, (size_t)n * qd * es);
     // O projection; its residual update is fused into the FFN norm when K is split
     if (L.s_o == 1) {

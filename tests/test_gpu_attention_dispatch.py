@@ -8,13 +8,13 @@ import pytest
 import torch
 
 from kernel_checks import U, half_ulp
-from paper_2606_29094_amd import engine
+from paper_2606_29094_amd import dlm, engine
 
 pytestmark = pytest.mark.gpu
 
 
-def _model(gpu, hq, hkv, dh, seed):
-    d, V, ffn = 128, 65, 64
+def _model(gpu, hq, hkv, dh, seed, ffn=64):
+    d, V = 128, 65
     g = torch.Generator().manual_seed(seed)
     mat = lambda r, c, s=0.1: (torch.randn(r, c, generator=g) * s).to(torch.bfloat16).to(gpu)
     one = lambda: torch.ones(d, device=gpu)
@@ -46,9 +46,38 @@ CASES = [
 ]
 
 
+# keys split over blocks; the partials lie where the FFN's activations go, so the
+# model's ffn is as wide as eight of them
+SPLIT_CASES = [
+    # more ranges than a short request has tiles (empty ranges), grouped queries
+    (28, 4, 128, [2000, 3, 70], 64, 64, "dual", "cache"),
+    # 17 tiles in ranges of three, the last tile of one key
+    (32, 32, 128, [961], 64, 32, "dual", "cache"),
+    # head_dim 64, a last block of one row, partly filled blocks
+    (8, 2, 64, [700, 1], 57, 57, "dual", "cache"),
+    # one row per head
+    (4, 4, 128, [513], 1, 1, "dual", "cache"),
+    # rows from the block to the end
+    (28, 4, 128, [900], 200, 64, "prefix", "cache"),
+    # three ranges over requests of very different lengths
+    (32, 32, 128, [1500, 40, 700], 64, 32, "dual", "cache"),
+]
+
+
 @pytest.mark.parametrize("hq,hkv,dh,prompts,gen,block,mode,kind", CASES)
 def test_attention_matches_fp64_on_its_inputs(gpu, hq, hkv, dh, prompts, gen, block, mode, kind):
-    model = _model(gpu, hq, hkv, dh, seed=sum(prompts))
+    _check(gpu, hq, hkv, dh, prompts, gen, block, mode, kind, 64)
+
+
+@pytest.mark.parametrize("hq,hkv,dh,prompts,gen,block,mode,kind", SPLIT_CASES)
+def test_split_keys_match_fp64_on_their_inputs(gpu, hq, hkv, dh, prompts, gen, block, mode, kind):
+    ran = _check(gpu, hq, hkv, dh, prompts, gen, block, mode, kind, 16 * hq * (dh + 2))
+    assert "attention_merge" in ran, ran
+
+
+def _check(gpu, hq, hkv, dh, prompts, gen, block, mode, kind, ffn):
+    """Checks one step's launch; returns the kernel classes that it ran."""
+    model = _model(gpu, hq, hkv, dh, sum(prompts), ffn)
     eng = engine.Engine(model, len(prompts), max(prompts) + gen, mode)
     eng.cache_buf.view(torch.bfloat16).fill_(float("nan"))
     rng = np.random.default_rng(2)
@@ -62,8 +91,10 @@ def test_attention_matches_fp64_on_its_inputs(gpu, hq, hkv, dh, prompts, gen, bl
         if kind == "mixed":
             reqs[0].refreshed_block = reqs[-1].refreshed_block = -1
     rows = eng.step_rows(reqs)
+    dlm.profile_enable(model.handle, True)
     buf, _ = eng.debug_trace(reqs, 0, logits=False)
     torch.cuda.synchronize()
+    classes = dlm.profile_read(model.handle)
     base = 0
     for r, (r0, r1) in zip(reqs, rows):
         n, L = r1 - r0, r.seq_len
@@ -83,3 +114,4 @@ def test_attention_matches_fp64_on_its_inputs(gpu, hq, hkv, dh, prompts, gen, bl
             err = half_ulp(np.abs(o) + slack, "bf16") + slack
             assert np.all(np.abs(got[:, h] - o) <= err), (r0, n, L, h)
         base += n
+    return set(classes)
