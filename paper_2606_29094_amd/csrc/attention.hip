@@ -709,8 +709,10 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
       }
     mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
     mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float m_new = fmaxf(m_run, mt);  // finite: key0 < L
-    const float alpha = expf(m_run - m_new);
+    const float m_new = fmaxf(m_run, mt);
+    // -inf while every score so far is (overflowed): weights of 0, not exp(-inf + inf)
+    const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = expf(m_run - m_ref);
     l_run *= alpha;
 #pragma unroll
     for (int j = 0; j < NDB; ++j) o[j] *= alpha;
@@ -719,13 +721,13 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float w = expf(s[b][e] - m_new);
+        const float w = expf(s[b][e] - m_ref);
         l_run += w;
 #pragma unroll
         for (int j = 0; j < NDB; ++j) o[j] = mfma16_f32(vf[b][j][e], w, o[j]);
       }
   }
-  // merge the waves' key groups (wave 0 always has keys)
+  // merge the waves' key groups
   xm[wave][lane] = m_run;
   xl[wave][lane] = l_run;
 #pragma unroll

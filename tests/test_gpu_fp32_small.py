@@ -80,3 +80,43 @@ def test_fp32_kernels_match_fp64_on_their_inputs(gpu, hq, hkv, dh, ffn, lens):
     slack = 1.1 * e[:, :ffn] * np.abs(y[:, ffn:]) + np.abs(y[:, :ffn]) * e[:, ffn:] \
         + e[:, :ffn] * e[:, ffn:] + 16 * U * np.abs(want)
     assert np.all(np.abs(buf["act"].double().cpu().numpy() - want) <= slack)
+
+
+@pytest.mark.parametrize("far", [(0, 32), (32, 64), (96, 224), (128, 256)])
+def test_fp32_key_group_whose_scores_overflow(gpu, far):
+    """Keys whose scores overflow to -inf get weight 0, also where they fill the
+    first 32-key group that a wave reads (the waves take the groups in turn)."""
+    d = dh = 64
+    L = 300
+    t = {"embed": torch.zeros(97, d), "lm_head": torch.zeros(97, d)}
+    t["embed"][:, 0] = 1.0                    # every token: q[31] of 5e19 to 8e19
+    t["embed"][1, 1] = 1.0                    # token 1: k[31] of about -6e19, scores of -inf
+    t["embed"][:, 2] = torch.linspace(-1, 1, 97)
+    w = torch.zeros(3 * dh, d)
+    w[31, 0], w[dh + 31, 1] = 1e19, -1e19     # the last rotary pair: its angle is 0 at every position
+    w[2 * dh:, 2] = torch.linspace(0.1, 1.0, dh)
+    one = torch.ones(d, device=gpu)
+    z = lambda r, c: torch.zeros(r, c, device=gpu)
+    dev = {k: v.to(gpu) for k, v in t.items()}
+    dev["final_norm"] = one
+    dev["layers"] = [{"attn_norm": one, "w_qkv": w.to(gpu), "w_o": z(d, dh), "ffn_norm": one,
+                      "w_gate_up": z(32, d), "w_down": z(d, 16)}]
+    shape = engine.ModelShape(1, d, 1, 1, dh, 16, 97, "f32", rope_theta=1e37)
+    model = engine.DeviceModel(shape, dev, 1.0)
+    eng = engine.Engine(model, 1, L, "none")
+    tok = np.arange(2, 2 + L).astype(np.int32) % 90 + 2
+    tok[far[0]:far[1]] = 1
+    r = engine.Request(tok[:L - 8], 8, 8, 0.9)
+    eng.admit(r, 96)
+    buf, _ = eng.debug_trace([r], 0, logits=False)
+    torch.cuda.synchronize()
+    k, v = (x.double().numpy()[:, 0] for x in eng.read_kv(0, r.slot, L))
+    q = buf["q"].double().cpu().numpy()
+    s = q @ k.T / np.sqrt(dh)
+    assert (s[:, far[0]:far[1]] < -1e38).all()          # -inf in fp32
+    assert np.abs(s[:, [i for i in range(L) if not far[0] <= i < far[1]]]).max() == 0
+    p = np.exp(s - s.max(1, keepdims=True))
+    o = (p / p.sum(1, keepdims=True)) @ v
+    got = buf["attn_out"].double().cpu().numpy()
+    # equal weights: L sums and products of fp32 values
+    assert np.all(np.abs(got - o) <= (L + 16) * U * np.abs(v).max())
