@@ -84,11 +84,8 @@ __global__ __launch_bounds__(QG* KG * 64) void attn_bf16_kernel(StepPlan p, cons
   // head-major grid: consecutive blocks (spread over the XCDs round-robin) are
   // different heads, so the query tiles of one head share one XCD's L2
   const int h = blockIdx.x, tile = blockIdx.y;
-  // request of this tile: tiles of QT rows are numbered request by request
-  int t0;
-  const int r = plan_req_of_qtile(p, tile, QT, &t0);
-  const ReqPlan& rq = p.r[r];
-  const int lrow0 = (tile - t0) * QT;
+  const ReqPlan& rq = p.r[plan_req_of_tile(p, tile)];
+  const int lrow0 = (tile - rq.tile0) * QT;
   const int nvalid = min(QT, rq.nrows - lrow0);
   const int L = rq.seq_len;
   const int kvh = h / (hq / hkv);
@@ -357,7 +354,7 @@ __host__ __device__ constexpr int shared_blocks(int nrows, int gh) {
 template <int DH, bool SPLIT>
 __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
     StepPlan p, const bf16* __restrict__ q, const bf16* __restrict__ kc,
-    const bf16* __restrict__ vc, int s_max, int hq, int hkv, int n_tiles, bf16* __restrict__ out,
+    const bf16* __restrict__ vc, int s_max, int hq, int hkv, bf16* __restrict__ out,
     float scale_log2, int splits, float* __restrict__ po, float2* __restrict__ ml) {
   constexpr int NW = kSharedWaves;
   constexpr int NT = NW * 64;
@@ -385,8 +382,8 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
     const int total = gridDim.x, id = blockIdx.x;
     const int xcd = id % kXcds, per = total / kXcds, rem = total % kXcds;
     const int lid = xcd * per + min(xcd, rem) + id / kXcds;
-    const int row = lid / n_tiles;                // (key/value head, split)
-    tile = lid - row * n_tiles;
+    const int row = lid / p.n_tiles;              // (key/value head, split)
+    tile = lid - row * p.n_tiles;
     if constexpr (SPLIT) {
       kvh = row / splits;
       split = row - kvh * splits;
@@ -394,18 +391,14 @@ __global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
       kvh = row;
     }
   }
-  // request of this tile: tiles of QT rows are numbered request by request
   const int gh = hq / hkv;
-  const int ln = threadIdx.x & 63;
-  int t0;
-  const int r = plan_req_of_lane_tiles(p, tile, ln < p.n_req ? shared_blocks(p.r[ln].nrows, gh) : 0, &t0);
-  const ReqPlan& rq = p.r[r];
+  const ReqPlan& rq = p.r[plan_req_of_tile(p, tile)];
   const int L = rq.seq_len;
   const bf16* kb = kc + ((long)(rq.slot * hkv + kvh) * s_max) * DH;
   const bf16* vb = vc + ((long)(rq.slot * hkv + kvh) * DH) * s_max;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int grp = (tile - t0) * NW + wave;        // this wave's (row group, head)
+  const int grp = (tile - rq.tile0) * NW + wave;        // this wave's (row group, head)
   const int row16 = grp / gh * 16;
   const int h = kvh * gh + grp % gh;              // query head
   const int qr = row16 + (lane & 15);             // query row of this lane in the request
@@ -653,12 +646,10 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
   __shared__ float xm[kF32Waves][64], xl[kF32Waves][64];
   __shared__ f32x4 xo[kF32Waves][NDB][64];
   const int tile = blockIdx.x, h = blockIdx.y;
-  int t0;
-  const int r = plan_req_of_qtile(p, tile, 16, &t0);
-  const ReqPlan& rq = p.r[r];
+  const ReqPlan& rq = p.r[plan_req_of_tile(p, tile)];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int g = lane >> 4, c = lane & 15;
-  const int qr = (tile - t0) * 16 + c;     // query row of this lane within the request
+  const int qr = (tile - rq.tile0) * 16 + c;     // query row of this lane within the request
   const bool q_ok = qr < rq.nrows;
   const long qrow = rq.row0 + min(qr, rq.nrows - 1);
   const int L = rq.seq_len;
@@ -758,12 +749,10 @@ template <int DH, int QG, int KG>
 static hipError_t launch_attn(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
                               int s_max, int hq, int hkv, bf16* out, float scale_log2,
                               hipStream_t st) {
-  constexpr int QT = 16 * QG;
-  int tiles = 0;
-  for (int r = 0; r < p.n_req; ++r) tiles += (p.r[r].nrows + QT - 1) / QT;
-  if (tiles == 0) return hipSuccess;
-  DLM_LAUNCH((attn_bf16_kernel<DH, QG, KG>), dim3(hq, tiles), dim3(QG * KG * 64), 0, st,
-                     p, q, kc, vc, s_max, hq, hkv, out, scale_log2);
+  const StepPlan t = plan_with_tiles(p, [](int n) { return ceil_div(n, 16 * QG); });
+  if (t.n_tiles == 0) return hipSuccess;
+  DLM_LAUNCH((attn_bf16_kernel<DH, QG, KG>), dim3(hq, t.n_tiles), dim3(QG * KG * 64), 0, st,
+                     t, q, kc, vc, s_max, hq, hkv, out, scale_log2);
   return hipGetLastError();
 }
 
@@ -771,15 +760,14 @@ template <int DH>
 static hipError_t launch_gqa(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
                              int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
                              float* scratch, hipStream_t st) {
-  int tiles = 0;
-  for (int r = 0; r < p.n_req; ++r) tiles += shared_blocks(p.r[r].nrows, hq / hkv);
-  if (tiles == 0) return hipSuccess;
+  const StepPlan t = plan_with_tiles(p, [&](int n) { return shared_blocks(n, hq / hkv); });
+  if (t.n_tiles == 0) return hipSuccess;
   if (splits == 1)
-    DLM_LAUNCH((attn_gqa_kernel<DH, false>), dim3(hkv * tiles), dim3(kSharedWaves * 64), 0, st, p,
-               q, kc, vc, s_max, hq, hkv, tiles, out, scale_log2, 1, nullptr, nullptr);
+    DLM_LAUNCH((attn_gqa_kernel<DH, false>), dim3(hkv * t.n_tiles), dim3(kSharedWaves * 64), 0, st,
+               t, q, kc, vc, s_max, hq, hkv, out, scale_log2, 1, nullptr, nullptr);
   else
-    DLM_LAUNCH((attn_gqa_kernel<DH, true>), dim3(hkv * tiles * splits), dim3(kSharedWaves * 64), 0,
-               st, p, q, kc, vc, s_max, hq, hkv, tiles, out, scale_log2, splits, scratch,
+    DLM_LAUNCH((attn_gqa_kernel<DH, true>), dim3(hkv * t.n_tiles * splits), dim3(kSharedWaves * 64),
+               0, st, t, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch,
                reinterpret_cast<float2*>(scratch + (size_t)splits * p.n_rows * hq * DH));
   return hipGetLastError();
 }
@@ -896,16 +884,15 @@ hipError_t attention<float>(const StepPlan& p, const float* q, const float* kc, 
                             int s_max, int hq, int hkv, int dh, float* out, int splits, float*,
                             hipStream_t st) {
   if (splits != 1) return hipErrorInvalidValue;
-  if (p.n_tiles == 0) return hipSuccess;
+  if (p.n_rows == 0) return hipSuccess;
   const float scale = 1.0f / sqrtf((float)dh);
-  int tiles = 0;
-  for (int r = 0; r < p.n_req; ++r) tiles += (p.r[r].nrows + 15) / 16;
-  dim3 g(tiles, hq);
+  const StepPlan t = plan_with_tiles(p, [](int n) { return ceil_div(n, 16); });
+  dim3 g(t.n_tiles, hq);
   if (dh == 64)
-    DLM_LAUNCH(attn_f32_kernel<64>, g, dim3(kF32Waves * 64), 0, st, p, q, kc, vc, s_max, hq, hkv,
+    DLM_LAUNCH(attn_f32_kernel<64>, g, dim3(kF32Waves * 64), 0, st, t, q, kc, vc, s_max, hq, hkv,
                        out, scale);
   else if (dh == 128)
-    DLM_LAUNCH(attn_f32_kernel<128>, g, dim3(kF32Waves * 64), 0, st, p, q, kc, vc, s_max, hq, hkv,
+    DLM_LAUNCH(attn_f32_kernel<128>, g, dim3(kF32Waves * 64), 0, st, t, q, kc, vc, s_max, hq, hkv,
                        out, scale);
   else
     return hipErrorInvalidValue;

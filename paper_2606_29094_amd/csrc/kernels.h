@@ -9,7 +9,7 @@ namespace dlm {
 constexpr int kMaxReq = 64;
 constexpr int kMaxBlock = 64;
 constexpr int kNStats = 8;      // confidence statistics per request
-constexpr int kQTile = 64;      // query rows per attention block / rows per RoPE tile
+constexpr int kQTile = 64;      // rows per RoPE tile
 
 // Per-request plan of one step, passed by value as a kernel argument.
 struct ReqPlan {
@@ -22,50 +22,50 @@ struct ReqPlan {
   int tok_off;   // offset of position 0 in tokens/mask
   int blk_s;     // active block [blk_s, blk_s + blk_len)
   int blk_len;
-  int tile0;     // first 64-row tile of this request (attention / RoPE grids)
+  int tile0;     // first tile of this request (kQTile rows; the attention launches number their own)
   int blk0;      // offset of this request's block rows in the packed block-row order
   float gamma;   // threshold
 };
 struct StepPlan {
   int n_req;
   int n_rows;    // total recompute rows N
-  int n_tiles;   // total 64-row tiles
+  int n_tiles;   // total tiles
   int n_blk;     // total block rows
   ReqPlan r[kMaxReq];
 };
 
-// Request of a packed row, of a 64-row tile, or of a tile of qt rows (tiles
-// numbered request by request; *t0: the request's first tile). Every lane of
-// the wave must be active: lane l looks at request l and a ballot counts those
-// that start at or before the row. (A walk over the requests is up to 64
-// dependent loads at the start of each block: 64 requests of 64 rows, RoPE and
-// key/value write 34 -> 20 us, attention 123 -> 117.)
+// Request of a packed row or of a tile (tiles numbered request by request,
+// ReqPlan::tile0). Every lane of the wave must be active. Lane l looks at request l
+// and a ballot counts those that start at or before the row (a walk over 64 requests
+// of 64 rows is 64 dependent loads at the start of each block: RoPE and key/value
+// write 34 us against 20, attention 123 against 117). One request needs no look-up:
+// the load and the ballot cost its launches 0.3-0.5 us (512 rows of 32 heads, RoPE
+// 11.6 / 11.3, attention 15.5 / 14.9); a scalar walk for up to 3, 4 or 8 requests was
+// no faster than the ballot (RoPE of 3 x 64 rows 7.6 / 7.3, of 8 x 64 13.3 / 11.8).
 static_assert(kMaxReq <= 64, "one lane per request");
-__device__ __forceinline__ int plan_req_of_row(const StepPlan& p, int row) {
+__device__ __forceinline__ int plan_req_at(const StepPlan& p, int ReqPlan::*start, int at) {
+  if (p.n_req == 1) return 0;
   const int lane = threadIdx.x & 63;
-  return __popcll(__ballot(lane < p.n_req && p.r[lane].row0 <= row)) - 1;
+  return __popcll(__ballot(lane < p.n_req && p.r[lane].*start <= at)) - 1;
+}
+__device__ __forceinline__ int plan_req_of_row(const StepPlan& p, int row) {
+  return plan_req_at(p, &ReqPlan::row0, row);
 }
 __device__ __forceinline__ int plan_req_of_tile(const StepPlan& p, int tile) {
-  const int lane = threadIdx.x & 63;
-  return __popcll(__ballot(lane < p.n_req && p.r[lane].tile0 <= tile)) - 1;
+  return plan_req_at(p, &ReqPlan::tile0, tile);
 }
-// nt: tiles of this lane's request (any numbering of tiles request by request)
-__device__ __forceinline__ int plan_req_of_lane_tiles(const StepPlan& p, int tile, int nt, int* t0) {
-  const int lane = threadIdx.x & 63;
-  int incl = nt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int v = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += v;
+// The same plan with its tiles numbered for another tile height, tiles(nrows) of each
+// request. (Filled on the host: a prefix sum over the lanes in every block took 0.3-0.6
+// us more, e.g. 64 rows over 1024 keys of 28/4 heads 9.4 / 8.8 us.)
+template <class F>
+inline StepPlan plan_with_tiles(const StepPlan& p, F tiles) {
+  StepPlan t = p;
+  t.n_tiles = 0;
+  for (int r = 0; r < t.n_req; ++r) {
+    t.r[r].tile0 = t.n_tiles;
+    t.n_tiles += tiles(t.r[r].nrows);
   }
-  const int r = __popcll(__ballot(lane < p.n_req && incl <= tile));
-  *t0 = __builtin_amdgcn_readlane(incl - nt, r);
-  return r;
-}
-__device__ __forceinline__ int plan_req_of_qtile(const StepPlan& p, int tile, int qt, int* t0) {
-  const int lane = threadIdx.x & 63;
-  const int nt = lane < p.n_req ? (p.r[lane].nrows + qt - 1) / qt : 0;
-  return plan_req_of_lane_tiles(p, tile, nt, t0);
+  return t;
 }
 
 // ---- GEMM family (gemm.hip, gemm_dl.hip) ----
