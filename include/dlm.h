@@ -327,6 +327,18 @@ dlm_status dlm_debug_gemm(int32_t cfg, int32_t epilogue, int32_t sub, int32_t n_
                           int32_t group_m, int32_t splits, const void* a, const void* b, void* c,
                           int32_t M, int32_t N, int32_t K, void* stream);
 
+/* Test hook for the attention dispatch (host only): the kernel (0 shared tiles,
+ * 1 shared tiles in blocks of four waves, 2 to 4 one query head per block with 32
+ * query rows and four key groups, 64 and two, 32 and two) and the number of key
+ * splits that a bf16 step would run for n_req requests of rows[r] recomputed
+ * rows over seq_len[r] keys, with scratch_bytes of scratch, on num_cu CUs.
+ * DLM_EINVAL for NULL arrays, n_req outside [1, 64], non-positive sizes, a
+ * head_dim other than 64 and 128, or n_q_heads not a multiple of n_kv_heads. */
+dlm_status dlm_debug_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                    int32_t n_req, const int32_t* rows, const int32_t* seq_len,
+                                    size_t scratch_bytes, int32_t num_cu, int32_t* kernel,
+                                    int32_t* splits);
+
 /* Kernel timing. While enabled, every kernel the library enqueues for this
  * model (or, when only_class is not NULL, every kernel of that class; see also
  * dlm_profile_sample) is timed by a pair of HIP events carried in the kernel's

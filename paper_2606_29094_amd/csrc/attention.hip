@@ -5,13 +5,14 @@
 // bf16 path (matrix cores), two kernels:
 //  * attn_gqa_kernel (shared tiles): one block = eight (16 query rows, query
 //    head) groups that read one key/value head of one request; 64-key tiles
-//    loaded directly into a two-stage LDS ring. Used where it makes at least a
-//    block per CU, and for few blocks over long sequences with the keys split
-//    over blocks, whose partials attn_merge_kernel adds.
+//    loaded directly into a two-stage LDS ring. For few blocks over long
+//    sequences the keys are split over blocks, whose partials attn_merge_kernel
+//    adds.
 //  * attn_bf16_kernel (per head): one block = 32 or 64 query rows of one request
 //    x one query head; waves split the rows in groups of 16 and the keys in
 //    four or two groups, tiles staged through registers. Used for launches with
-//    few blocks that a key split does not pay for (one request's no-cache step).
+//    few blocks that a key split does not pay for.
+//  attention_plan chooses.
 // Key tiles are staged in LDS keys row-major and values transposed, which is
 // how the cache stores them.
 // Each wave computes S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (keys as the A
@@ -345,18 +346,17 @@ __global__ __launch_bounds__(QG* KG * 64) void attn_bf16_kernel(StepPlan p, cons
 // set to -inf and their V^T entries cleared in LDS.
 constexpr int kSharedWaves = 8;
 // blocks of a request per key/value head
-__host__ __device__ constexpr int shared_blocks(int nrows, int gh) {
-  return ceil_div(ceil_div(nrows, 16) * gh, kSharedWaves);
+__host__ __device__ constexpr int shared_blocks(int nrows, int gh, int waves) {
+  return ceil_div(ceil_div(nrows, 16) * gh, waves);
 }
 // SPLIT: blockIdx also counts the key splits, each a contiguous range of the
 // request's key tiles; a block leaves its unnormalised O and (m, l) of every
 // (row, head) in po and ml, [split][row][head], for attn_merge_kernel.
-template <int DH, bool SPLIT>
-__global__ __launch_bounds__(kSharedWaves * 64) void attn_gqa_kernel(
+template <int DH, bool SPLIT, int NW>
+__global__ __launch_bounds__(NW * 64) void attn_gqa_kernel(
     StepPlan p, const bf16* __restrict__ q, const bf16* __restrict__ kc,
     const bf16* __restrict__ vc, int s_max, int hq, int hkv, bf16* __restrict__ out,
     float scale_log2, int splits, float* __restrict__ po, float2* __restrict__ ml) {
-  constexpr int NW = kSharedWaves;
   constexpr int NT = NW * 64;
   constexpr int SK = 64;                   // keys per tile
   constexpr int KRB = DH * 2;              // K row bytes
@@ -756,99 +756,119 @@ static hipError_t launch_attn(const StepPlan& p, const bf16* q, const bf16* kc, 
   return hipGetLastError();
 }
 
-template <int DH>
-static hipError_t launch_gqa(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                             int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
-                             float* scratch, hipStream_t st) {
-  const StepPlan t = plan_with_tiles(p, [&](int n) { return shared_blocks(n, hq / hkv); });
+template <int DH, bool SPLIT, int NW>
+static hipError_t launch_shared(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
+                                int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
+                                float* scratch, hipStream_t st) {
+  const StepPlan t = plan_with_tiles(p, [&](int n) { return shared_blocks(n, hq / hkv, NW); });
   if (t.n_tiles == 0) return hipSuccess;
-  if (splits == 1)
-    DLM_LAUNCH((attn_gqa_kernel<DH, false>), dim3(hkv * t.n_tiles), dim3(kSharedWaves * 64), 0, st,
-               t, q, kc, vc, s_max, hq, hkv, out, scale_log2, 1, nullptr, nullptr);
-  else
-    DLM_LAUNCH((attn_gqa_kernel<DH, true>), dim3(hkv * t.n_tiles * splits), dim3(kSharedWaves * 64),
-               0, st, t, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch,
-               reinterpret_cast<float2*>(scratch + (size_t)splits * p.n_rows * hq * DH));
+  DLM_LAUNCH((attn_gqa_kernel<DH, SPLIT, NW>), dim3(hkv * t.n_tiles * splits), dim3(NW * 64), 0, st,
+             t, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch,
+             reinterpret_cast<float2*>(scratch + (size_t)splits * p.n_rows * hq * DH));
   return hipGetLastError();
 }
 
-// Which kernel where attention_splits leaves the keys whole (times are one layer's launch on MI355X, 256 CUs, head_dim 128,
-// chosen kernel against the other):
-//  * The shared-tile kernel with at least 256 blocks (28/4 heads, 16 x 64 rows
-//    over 1024 keys: 38 us against 51; 32 heads, 1476 rows 74 / 97, 8 x 128 rows
-//    over 1152 keys 41 / 56), or where the per-head kernel's 64-row blocks pass one
-//    per CU and a second round of them starts (32 heads, 560 rows 21.8 / 32.7, 960
-//    33.4 / 46.7; 28/4 heads, 600 rows 22.5 / 33.3, 1100 38.8 / 52.9). With
-//    fewer, CUs idle behind a serial key walk
-//    (28/4 heads, 3 x 64 rows over 2300 keys 35 / 69, 8 x 64 over 1024 27 / 35; 32
-//    heads, 512 rows 16 / 20). Where no request has more than 32 rows its
-//    blocks compute in two waves of eight and are read-bound: 512 blocks (32 heads,
-//    8 x 32 rows over 1280 keys 36.6 / 37.7, 16 x 32 71.1 / 69.8), and over short
-//    sequences its loads by all eight waves win at any count (32 rows over 200 keys
-//    10.4 / 12.3, over 517 16.9 / 18.5, over 2300 47.6 / 39.9); over up to three key
-//    tiles, less than one of the per-head kernel's four-group turns, they do for any
-//    rows and heads (32 heads, 64 rows over 64 keys 5.5 / 10.9, 192 over 192 9.8 / 10.5;
-//    28/4 heads 7.0 / 10.6, 10.3 / 11.0).
-//  * Otherwise the per-head kernel: 32 query rows and four key groups (8 waves)
-//    while that is at most one block per CU or no request has more than 32 rows
-//    (32 rows over 2300 keys 40 us, with two key groups 45), else 64 rows and two
-//    key groups (512 rows 16.4 us, with 32-row blocks 23).
 template <int DH>
 static hipError_t attention_dh(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                               int s_max, int hq, int hkv, bf16* out, float scale_log2, int splits,
-                               float* scratch, hipStream_t st) {
-  if (hkv < 1 || hq % hkv != 0 || splits < 1 || splits > kMaxSplits) return hipErrorInvalidValue;
-  if (splits > 1)
-    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
-  int max_rows = 0, max_len = 0;
-  long shared = 0, t32 = 0, t64 = 0;
-  for (int r = 0; r < p.n_req; ++r) {
-    const int n = p.r[r].nrows;
-    max_rows = max(max_rows, n);
-    max_len = max(max_len, p.r[r].seq_len);
-    shared += (long)hkv * shared_blocks(n, hq / hkv);
-    t32 += ceil_div(n, 32);
-    t64 += ceil_div(n, 64);
+                               int s_max, int hq, int hkv, bf16* out, float scale_log2,
+                               AttnPlan plan, float* scratch, hipStream_t st) {
+  if (hkv < 1 || hq % hkv != 0 || plan.splits < 1 || plan.splits > kMaxSplits ||
+      (plan.splits > 1 && plan.kernel != kAttnShared))
+    return hipErrorInvalidValue;
+#define ATTN_HEAD(QG_, KG_) launch_attn<DH, QG_, KG_>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st)
+#define ATTN_SHARED(SPLIT_, NW_)                                                            \
+  launch_shared<DH, SPLIT_, NW_>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, plan.splits, \
+                                 scratch, st)
+  switch (plan.kernel) {
+    case kAttnShared:
+      return plan.splits > 1 ? ATTN_SHARED(true, kSharedWaves) : ATTN_SHARED(false, kSharedWaves);
+    case kAttnHead32x4: return ATTN_HEAD(2, 4);
+    case kAttnHead64x2: return ATTN_HEAD(4, 2);
+    default: break;
   }
-  const bool few = max_rows <= 32;
-  const bool brief = DH == 128 && (max_len <= 192 || (few && max_len <= 640 && hq == hkv));
-  if (brief || shared >= (few ? 512 : 256) || (!few && hq * t64 > 256))
-    return launch_gqa<DH>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, 1, nullptr, st);
-  return few || hq * t32 <= 256
-             ? launch_attn<DH, 2, 4>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st)
-             : launch_attn<DH, 4, 2>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, st);
+  if constexpr (DH == 64) {
+    if (plan.kernel == kAttnShared4) return ATTN_SHARED(false, 4);
+    if (plan.kernel == kAttnHead32x2) return ATTN_HEAD(2, 2);
+  }
+#undef ATTN_SHARED
+#undef ATTN_HEAD
+  return hipErrorInvalidValue;
 }
 
-// Key splits of the shared-tile kernel, so that a launch of few blocks fills
-// the CUs instead of walking all keys in each. As many as make about a block per
-// CU (288: 96 blocks take 3 splits), where the longest walk gets shorter by enough key
-// tiles, about 1 us each, to pay for the merge launch (4 us, and the partials' way
-// through memory: a tile per 16384 (row, head, split)). One layer's launch and merge
-// against the unsplit kernel chosen below, MI355X, head_dim 128:
-//   32 heads: 32 rows over 517 keys 6.8 + 4.0 us against 15.5, over 2300 14.7 + 4.1
-//     / 42, 2 x 57 rows over 1200 13.5 + 4.1 / 28, 4 x 32 over 1280 22.2 + 4.1 / 28.1
-//   28/4 heads: 64 rows over 900 keys 8.0 + 4.0 / 21.6, 4 x 57 over 2300 26.0 + 4.1
-//     / 46.5, 8 x 32 over 600 13.8 + 4.3 / 22.6, 8 x 64 over 1024 22.4 + 4.4 / 28.0
-//   left unsplit: 32 heads, 32 rows over 200 keys 6.3 + 4.1 / 9.1, 200 rows over 200
-//     9.8 + 4.3 / 11.4, 512 rows over 512 15.1 + 4.6 / 16.0, 8 x 32 over 1280 36.6 + 4.3
-//     / 37.8; 28/4 heads, 512 rows over 512 15.3 + 4.4 / 15.5
-int attention_splits(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
-                     size_t scratch_bytes) {
-  if (elem != 2 || hkv < 1 || hq % hkv != 0) return 1;
-  int max_len = 0;
-  long blocks = 0;
+// Kernel and key splits of a bf16 launch. Times are one layer's launch on MI355X
+// (256 CUs) with cold caches, in us; head_dim 128 unless stated. What decides: blocks
+// per CU; whether more than half of a shared-tile block's eight waves have rows
+// ("full"); and the key tiles of 64 that a block walks one after the other.
+//  * Key splits (shared tiles; attn_merge_kernel adds 4 us, and the partials' way
+//    through memory a key tile's time per 16384 (row, head, split)) where the walk
+//    gets shorter by enough tiles, about 1 us each: 5; 11 for multi-head head_dim
+//    64, whose tiles take half as long; 4 more where the per-head kernel below fills
+//    half the CUs. As many ranges as make a block per CU (28/4 heads, 8 x 48 rows
+//    over 1280 keys, 96 blocks: two ranges 29.0, three 32.6, whole 31.9), or 9/8 of
+//    that where blocks are not full (32 heads, 3 x 16 over 2304, 96 blocks: three
+//    29.3, two 31.6). 32 x 517 6.8 + 4.0 against 15.5, 28/4 heads, 64 x 900 8.0 + 4.0
+//    / 21.6; left whole: 512 x 512 15.1 + 4.6 / 16.0, head_dim 64, 2 x 200 over 1280
+//    20.8 / 18.8.
+//  * At most 32 rows per request: grouped queries fill the shared-tile blocks
+//    (28/4, 20 x 32 over 1280 shared 40, per head 76; 48 x 16 over 320 15 / 90).
+//    Multi-head: shared tiles over short sequences (8 x 32 over 640 20 / 26) and
+//    where the per-head blocks start a second round (10 x 32 over 1280 43 /
+//    56, 16 x 32 67 / 71, 20 x 32 98 / 94, 6 x 32 over 2304 52 / 47). head_dim 64:
+//    per-head blocks of four waves, which fit twice as often on a CU (20 x 32 over
+//    1280 shared 52, four key groups 49, two 44; 8 x 32 over 320 7.8 / 11.2 /
+//    10.9); four key groups for long sequences (8 x 32 over 2304 30.7 / 32.5).
+//  * head_dim 64, multi-head, at most 64 rows per request, more than two blocks
+//    per CU: shared-tile blocks of four waves (20 x 64 over 1280 42.6, eight 53.4,
+//    per head 48.8).
+//  * Over one or three key tiles, or up to five in blocks that are not full: shared
+//    (32 heads, 4 x 64 over 320 10.9 / 14.2; 128 rows over 128, full: 7.7 / 7.0;
+//    160 over 160 10.0 / 10.8).
+//  * Otherwise the per-head kernel while its blocks fit in one round: 32 rows and
+//    four key groups where the 256-key turns are full (32 heads, 256 rows over 256
+//    8.1 / 9.1; 200 over 200 10.9 / 10.8), else 64 rows and two (512 rows 14.7,
+//    shared 17.6); then shared tiles (600 rows 21.7 / 32.5, 1024 34.3 / 44.7).
+AttnPlan attention_plan(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
+                        size_t scratch_bytes, int num_cu) {
+  if (elem != 2 || hkv < 1 || hq % hkv != 0 || p.n_rows < 1) return AttnPlan{};
+  const int gh = hq / hkv;
+  int max_rows = 0, max_len = 0;
+  long blocks = 0, groups = 0, t32 = 0, t64 = 0;
   for (int r = 0; r < p.n_req; ++r) {
-    max_len = max(max_len, p.r[r].seq_len);
-    blocks += (long)hkv * shared_blocks(p.r[r].nrows, hq / hkv);
+    const int n = p.r[r].nrows;
+    max_rows = std::max(max_rows, n);
+    max_len = std::max(max_len, p.r[r].seq_len);
+    blocks += (long)hkv * shared_blocks(n, gh, kSharedWaves);
+    groups += (long)hq * ceil_div(n, 16);
+    t32 += (long)hq * ceil_div(n, 32);
+    t64 += (long)hq * ceil_div(n, 64);
   }
-  if (blocks == 0) return 1;
+  const int nt = ceil_div(max_len, 64);
+  const bool few = max_rows <= 32, mha = gh == 1, narrow = dh == 64;
+  const bool full = 2 * groups > blocks * kSharedWaves;
+
+  const long room = full ? num_cu : num_cu + num_cu / 8;
   const size_t one = (size_t)p.n_rows * hq * (dh * sizeof(float) + sizeof(float2));
-  const long room = (long)std::min((size_t)kMaxSplits, scratch_bytes / one);
-  const int s = (int)std::min(288 / blocks, room);
-  if (s < 2) return 1;
-  const int nt = ceil_div(max_len, 64), per = ceil_div(nt, s);
-  if (nt - per < 5 + (long)p.n_rows * hq * s / 16384) return 1;
-  return ceil_div(nt, per);
+  long s = std::min({(long)kMaxSplits, room / blocks, (long)(scratch_bytes / one)});
+  for (; s > 1; --s) {                     // ranges of equal length: as many as are not empty
+    const int per = ceil_div(nt, (int)s), used = ceil_div(nt, per);
+    if (blocks * used > room) continue;
+    const long need = (narrow && mha ? 11 : 5) +
+                      (full && !few && t64 <= num_cu && 2 * t64 > num_cu ? 4 : 0) +
+                      (long)p.n_rows * hq * used * dh / (128 * 16384);
+    if (used > 1 && nt - per >= need) return AttnPlan{kAttnShared, used};
+    break;
+  }
+  if (few) {
+    if (!mha || nt <= (narrow ? 5 : 10)) return AttnPlan{kAttnShared, 1};
+    if (narrow)
+      return AttnPlan{nt >= 16 && t32 <= num_cu ? kAttnHead32x4 : kAttnHead32x2, 1};
+    return AttnPlan{t32 > num_cu && t32 <= 2 * num_cu ? kAttnShared : kAttnHead32x4, 1};
+  }
+  if (narrow && mha && max_rows <= 64 && t64 > 2 * num_cu) return AttnPlan{kAttnShared4, 1};
+  if (nt == 1 || nt == 3 || (nt <= 5 && !full)) return AttnPlan{kAttnShared, 1};
+  const int turns = ceil_div(max_len, 256) * 256;
+  if (t32 <= num_cu && nt >= 4 && (turns - max_len) * 8 <= turns) return AttnPlan{kAttnHead32x4, 1};
+  return AttnPlan{t64 <= num_cu ? kAttnHead64x2 : kAttnShared, 1};
 }
 
 hipError_t attention_merge(const StepPlan& p, int hq, int dh, int splits, const float* scratch,
@@ -870,20 +890,20 @@ hipError_t attention_merge(const StepPlan& p, int hq, int dh, int splits, const 
 
 template <>
 hipError_t attention<bf16>(const StepPlan& p, const bf16* q, const bf16* kc, const bf16* vc,
-                           int s_max, int hq, int hkv, int dh, bf16* out, int splits,
+                           int s_max, int hq, int hkv, int dh, bf16* out, AttnPlan plan,
                            float* scratch, hipStream_t st) {
   if (p.n_rows == 0) return hipSuccess;
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
-  if (dh == 128) return attention_dh<128>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
-  if (dh == 64) return attention_dh<64>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, splits, scratch, st);
+  if (dh == 128) return attention_dh<128>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, plan, scratch, st);
+  if (dh == 64) return attention_dh<64>(p, q, kc, vc, s_max, hq, hkv, out, scale_log2, plan, scratch, st);
   return hipErrorInvalidValue;
 }
 
 template <>
 hipError_t attention<float>(const StepPlan& p, const float* q, const float* kc, const float* vc,
-                            int s_max, int hq, int hkv, int dh, float* out, int splits, float*,
+                            int s_max, int hq, int hkv, int dh, float* out, AttnPlan plan, float*,
                             hipStream_t st) {
-  if (splits != 1) return hipErrorInvalidValue;
+  if (plan.splits != 1) return hipErrorInvalidValue;
   if (p.n_rows == 0) return hipSuccess;
   const float scale = 1.0f / sqrtf((float)dh);
   const StepPlan t = plan_with_tiles(p, [](int n) { return ceil_div(n, 16); });

@@ -168,15 +168,19 @@ hipError_t unmask_select(const StepPlan& p, const float* conf, const int* tok,
                          float* stats, hipStream_t st);
 
 // ---- attention (attention.hip) ----
-// splits > 1 (bf16): every block takes one of that many key ranges and leaves its
-// partial in scratch; attention_merge then writes out. splits comes from
-// attention_splits for the step's plan, which keeps the partials within
-// scratch_bytes (16-byte aligned; 1: scratch is not used).
-int attention_splits(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
-                     size_t scratch_bytes);
+// Kernels of a bf16 launch: shared tiles in blocks of eight or four waves; one query
+// head per block with 32 rows and four key groups, 64 and two, 32 and two (the
+// four-wave blocks for head_dim 64 only). splits > 1 (kAttnShared): every block takes
+// one of that many key ranges and leaves its partial in scratch; attention_merge
+// then writes out. attention_plan keeps the partials of the step within
+// scratch_bytes (16-byte aligned; splits 1: scratch is not used). fp32: one kernel.
+enum AttnKernel { kAttnShared, kAttnShared4, kAttnHead32x4, kAttnHead64x2, kAttnHead32x2 };
+struct AttnPlan { AttnKernel kernel = kAttnShared; int splits = 1; };
+AttnPlan attention_plan(const StepPlan& p, int hq, int hkv, int dh, size_t elem,
+                        size_t scratch_bytes, int num_cu);
 template <typename T>
 hipError_t attention(const StepPlan& p, const T* q, const T* kcache, const T* vcache,
-                     int s_max, int hq, int hkv, int dh, T* out, int splits, float* scratch,
+                     int s_max, int hq, int hkv, int dh, T* out, AttnPlan plan, float* scratch,
                      hipStream_t st);
 hipError_t attention_merge(const StepPlan& p, int hq, int dh, int splits, const float* scratch,
                            bf16* out, hipStream_t st);

@@ -379,7 +379,7 @@ dlm_status run_forward(dlm_model* m, dlm_cache* c, const dlm_batch* b, const Ste
   float* part = reinterpret_cast<float*>(ws + L.part);
   T* act = reinterpret_cast<T*>(ws + L.act);
   // part and act (consecutive) hold nothing while attention runs: its key splits' partials go there
-  const int ksplit = attention_splits(p, hq, hkv, dh, sizeof(T), L.lm_rows - L.part);
+  const AttnPlan ap = attention_plan(p, hq, hkv, dh, sizeof(T), L.lm_rows - L.part, m->num_cu);
 
   LAUNCH(m, st, "embed_norm", embed_norm_rows<T>(p, reinterpret_cast<const T*>(m->embed), d, cf.vocab,
                          cf.mask_id, b->tokens, b->mask, m->layers[0].attn_norm, cf.rms_eps, dh,
@@ -400,10 +400,10 @@ dlm_status run_forward(dlm_model* m, dlm_cache* c, const dlm_batch* b, const Ste
     LAUNCH(m, st, "rope_kv_write", qkv_rope_scatter<T>(p, qkv, L.s_qkv, (long)n * qkv_dim, cs, hq, hkv, dh, q, kc, vc,
                                  c->s_max, st));
     if (t) TRACE_COPY(t->q, q, (size_t)n * qd * es);
-    LAUNCH(m, st, "attention", attention<T>(p, q, kc, vc, c->s_max, hq, hkv, dh, ao, ksplit, part, st));
+    LAUNCH(m, st, "attention", attention<T>(p, q, kc, vc, c->s_max, hq, hkv, dh, ao, ap, part, st));
     if constexpr (sizeof(T) == 2)
-      if (ksplit > 1)
-        LAUNCH(m, st, "attention_merge", attention_merge(p, hq, dh, ksplit, part, ao, st));
+      if (ap.splits > 1)
+        LAUNCH(m, st, "attention_merge", attention_merge(p, hq, dh, ap.splits, part, ao, st));
     if (t) TRACE_COPY(t->attn_out, ao, (size_t)n * qd * es);
     // O projection; its residual update is fused into the FFN norm when K is split
     if (L.s_o == 1) {
@@ -801,6 +801,32 @@ dlm_status dlm_head_confidence(dlm_model* m, const void* u_rows, int32_t m_rows,
                                  cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, nullptr, st));
   }
   HIPCHECK(lm_combine(pm, ps, pi, tiles, m_rows, nullptr, m_rows, conf, tok, st));
+  return DLM_OK;
+}
+
+dlm_status dlm_debug_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim,
+                                    int32_t n_req, const int32_t* rows, const int32_t* seq_len,
+                                    size_t scratch_bytes, int32_t num_cu, int32_t* kernel,
+                                    int32_t* splits) {
+  g_err.clear();
+  if (!rows || !seq_len) return fail(DLM_EINVAL, "NULL array");
+  if (n_req < 1 || n_req > kMaxReq) return fail(DLM_EINVAL, "n_req %d outside [1, %d]", n_req, kMaxReq);
+  if (n_q_heads < 1 || n_kv_heads < 1 || n_q_heads % n_kv_heads != 0 || num_cu < 1 ||
+      (head_dim != 64 && head_dim != 128))
+    return fail(DLM_EINVAL, "heads %d / %d of %d on %d CUs", n_q_heads, n_kv_heads, head_dim, num_cu);
+  StepPlan p{};
+  p.n_req = n_req;
+  for (int r = 0; r < n_req; ++r) {
+    if (rows[r] < 1 || seq_len[r] < 1)
+      return fail(DLM_EINVAL, "request %d: %d rows over %d keys", r, rows[r], seq_len[r]);
+    p.r[r].row0 = p.n_rows;
+    p.r[r].nrows = rows[r];
+    p.r[r].seq_len = seq_len[r];
+    p.n_rows += rows[r];
+  }
+  const AttnPlan ap = attention_plan(p, n_q_heads, n_kv_heads, head_dim, 2, scratch_bytes, num_cu);
+  if (kernel) *kernel = ap.kernel;
+  if (splits) *splits = ap.splits;
   return DLM_OK;
 }
 

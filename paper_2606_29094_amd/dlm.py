@@ -27,6 +27,7 @@ EXPORTS = ["dlm_load_weights", "dlm_model_destroy", "dlm_workspace_bytes",
            "dlm_kv_cache_alloc", "dlm_cache_destroy", "dlm_cache_invalidate",
            "dlm_denoise_step", "dlm_denoise_step_noalloc", "dlm_cache_refresh",
            "dlm_debug_logits", "dlm_debug_trace", "dlm_debug_gemm_info", "dlm_debug_gemm",
+           "dlm_debug_attention_plan",
            "dlm_head_confidence", "dlm_profile_enable", "dlm_profile_read",
            "dlm_profile_sample", "dlm_ceiling_mfma", "dlm_ceiling_copy", "dlm_last_error"]
 
@@ -124,6 +125,9 @@ def lib():
         L.dlm_debug_gemm.argtypes = [c_int32, c_int32, c_int32, c_int32, c_int32, c_int32,
                                      c_void_p, c_void_p, c_void_p, c_int32, c_int32, c_int32,
                                      c_void_p]
+        L.dlm_debug_attention_plan.argtypes = [c_int32, c_int32, c_int32, c_int32,
+                                               POINTER(c_int32), POINTER(c_int32), c_size_t,
+                                               c_int32, POINTER(c_int32), POINTER(c_int32)]
         L.dlm_profile_enable.argtypes = [c_void_p, c_int32, ctypes.c_char_p]
         L.dlm_profile_read.argtypes = [c_void_p, POINTER(DlmProfileEntry), c_int32,
                                        POINTER(c_int32)]
@@ -137,7 +141,7 @@ def lib():
                      "dlm_cache_invalidate", "dlm_denoise_step", "dlm_denoise_step_noalloc",
                      "dlm_cache_refresh",
                      "dlm_debug_logits", "dlm_debug_trace", "dlm_head_confidence",
-                     "dlm_debug_gemm_info", "dlm_debug_gemm",
+                     "dlm_debug_gemm_info", "dlm_debug_gemm", "dlm_debug_attention_plan",
                      "dlm_profile_enable",
                      "dlm_profile_read", "dlm_profile_sample"]:
             getattr(L, name).restype = c_int32
@@ -273,6 +277,17 @@ def debug_gemm_info(cfg: int):
     if rc != DLM_OK:
         return None
     return bm.value, bn.value, subs.value
+
+
+def debug_attention_plan(hq: int, hkv: int, dh: int, rows, lens, scratch_bytes: int,
+                         num_cu: int = 256):
+    """(kernel, key splits) of a bf16 step's attention (dlm_debug_attention_plan)."""
+    arr = lambda v: (c_int32 * len(v))(*v)
+    kernel, splits = c_int32(), c_int32()
+    check(lib().dlm_debug_attention_plan(hq, hkv, dh, len(rows), arr(rows), arr(lens),
+                                         scratch_bytes, num_cu, ctypes.byref(kernel),
+                                         ctypes.byref(splits)))
+    return kernel.value, splits.value
 
 
 def debug_gemm(cfg: int, epilogue: int, a, b, c, sub: int = 0, n_tail: int = 0,

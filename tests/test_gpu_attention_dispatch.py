@@ -34,15 +34,32 @@ CASES = [
     # shared tiles over short sequences, one block of 32 rows per head
     (32, 32, 128, [200], 64, 32, "dual", "cache"),
     (8, 8, 128, [1, 576], 64, 31, "dual", "cache"),
-    # per head, 32 rows and four key groups: fewer keys than groups, several turns
+    # fewer keys than a tile
     (4, 4, 64, [5], 9, 9, "dual", "cache"),
+    # per head, 32 rows and four key groups: several turns
     (8, 8, 128, [900, 641], 64, 32, "dual", "cache"),
+    # per head, 64 rows and two key groups: grouped queries, multi-head
     (28, 4, 128, [400, 20, 130], 200, 64, "dual", "cache"),
-    # per head, 64 rows and two key groups (more than 256 blocks of 32 rows)
     (32, 32, 128, [256], 256, 32, "none", "refresh"),
     # cache and recompute requests in one launch
     (32, 32, 128, [300, 40, 700, 128, 90, 511], 64, 32, "dual", "mixed"),
     (28, 4, 64, [300, 40, 700, 128], 64, 64, "dual", "mixed"),
+]
+
+
+# each kernel at the edges of its tiles, with the number that dlm_debug_attention_plan
+# gives it
+FORMS = [
+    # grouped queries of at most 32 rows: two row groups x seven heads in two blocks
+    (0, 28, 4, 128, [300, 31, 500, 1, 65, 64, 400, 129, 77, 700, 250, 33, 511, 40, 200], 48, 17,
+     "dual", "cache"),
+    # four-wave shared-tile blocks: more than two per CU, requests of one to four row groups
+    (1, 32, 32, 64, [64 + 9 * i for i in range(17)], 64, 57, "dual", "cache"),
+    # per head, 32 rows and four key groups: rows to a tile's edge, one turn and a row less
+    (2, 8, 8, 128, [192], 64, 64, "none", "refresh"),
+    (2, 4, 2, 64, [230, 191], 25, 25, "none", "refresh"),
+    # per head, 32 rows and two key groups: an odd tile, fewer keys than a turn in one request
+    (4, 8, 8, 64, [700, 1, 321], 33, 17, "dual", "cache"),
 ]
 
 
@@ -66,6 +83,15 @@ SPLIT_CASES = [
 
 @pytest.mark.parametrize("hq,hkv,dh,prompts,gen,block,mode,kind", CASES)
 def test_attention_matches_fp64_on_its_inputs(gpu, hq, hkv, dh, prompts, gen, block, mode, kind):
+    _check(gpu, hq, hkv, dh, prompts, gen, block, mode, kind, 64)
+
+
+@pytest.mark.parametrize("kernel,hq,hkv,dh,prompts,gen,block,mode,kind", FORMS)
+def test_each_kernel_matches_fp64_on_its_inputs(gpu, kernel, hq, hkv, dh, prompts, gen, block, mode,
+                                                kind):
+    lens = [p + gen for p in prompts]
+    rows = lens if kind == "refresh" else [min(block, gen)] * len(lens)
+    assert dlm.debug_attention_plan(hq, hkv, dh, rows, lens, 0) == (kernel, 1)
     _check(gpu, hq, hkv, dh, prompts, gen, block, mode, kind, 64)
 
 
