@@ -327,6 +327,16 @@ dlm_status dlm_debug_gemm(int32_t cfg, int32_t epilogue, int32_t sub, int32_t n_
                           int32_t group_m, int32_t splits, const void* a, const void* b, void* c,
                           int32_t M, int32_t N, int32_t K, void* stream);
 
+/* Test hook for the GEMM planner (host only): the plan of a launch of M rows,
+ * weights [N, K] of elem_bytes (2 bf16, 4 fp32), on num_cu CUs; kind 0: a
+ * projection whose K may be split, 1: gate/up (N = 2 d_ffn), 2: the LM head.
+ * out = tile configuration (negative: a register-staged kernel, -2 the small-tile
+ * fp32 one), K slices, sub-tiles per tile of the last round (0: whole), tiles run
+ * as sub-tiles. DLM_EINVAL for a NULL out, another kind or element size, or
+ * non-positive sizes. */
+dlm_status dlm_debug_gemm_plan(int32_t elem_bytes, int32_t M, int32_t N, int32_t K, int32_t kind,
+                               int32_t num_cu, int32_t out[4]);
+
 /* Test hook for the attention dispatch (host only): the kernel (0 shared tiles,
  * 1 shared tiles in blocks of four waves, 2 to 4 one query head per block with 32
  * query rows and four key groups, 64 and two, 32 and two) and the number of key

@@ -16,6 +16,7 @@
 // v_mfma_f32_16x16x32_bf16, fp32 uses v_mfma_f32_16x16x4_f32 (four per 16-byte
 // fragment, the k order is the same permutation for A and B).
 #include <algorithm>
+#include <cmath>
 
 #include "common.h"
 #include "gemm_common.h"
@@ -252,7 +253,7 @@ static hipError_t launch(const GemmPlan& p, const T* A, int lda, const T* B, int
 // MHA QKV projection). The cheapest
 // (configuration, split) wins. 128x192 with two blocks per CU (cfg 22) runs
 // without K splits only (its table holds unsplit launches). Up to 1024 rows
-// the tables of kFewRowTables apply instead. The eight-wave configurations run the split-phase tile
+// the model of kFewRowTiles applies instead. The eight-wave configurations run the split-phase tile
 // form with a three-stage weight ring (6, 21, 70) or three stages of both
 // operands (29); their tables are the ones measured for their two-ring form,
 // each entry scaled by the time ratios of the forms measured at that k-tile
@@ -285,7 +286,7 @@ const RoundTable kRoundTables[] = {
     {42, 1, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {14.6f, 18.1f, 20.7f, 29.2f, 27.6f, 32.4f, 41.1f, 47.7f, 47.8f, 56.8f, 70.6f, 80.0f, 124.7f, 154.4f, 232.9f}},
-    // (LM head only: the projections of up to 1024 rows use the tables below)
+    // (LM head only: the projections of up to 1024 rows use the model below)
     {1, 2, false, 15,
      {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296},
      {17.1f, 22.4f, 25.6f, 37.3f, 33.5f, 40.8f, 51.1f, 65.7f, 65.8f, 71.1f, 90.8f, 119.1f, 171.0f, 214.9f, 335.1f},
@@ -311,71 +312,88 @@ const RoundTable kRoundTables[] = {
      {22.5f, 25.7f, 31.3f, 45.6f, 42.3f, 51.5f, 64.1f, 71.1f, 70.6f, 94.1f, 111.6f, 126.1f, 192.8f, 234.0f, 374.4f}},
 };
 
-// Launches of up to kFewRows (kernels.h) rows: every configuration that wins somewhere
-// there, timed in one run (MI355X, the eight projection shapes of both models,
-// 16 row counts from 8 to 1024, 1 to 8 K slices, weights streamed from HBM:
-// 7158 launches). us1[i] is the median time of a launch of 151 to 256 blocks
-// whose blocks walk kFewKt[i] k-tiles, us2 that of 384 to 512 blocks of the
-// configuration whose blocks fit twice on a CU (64 KB of LDS). Over the shapes
-// and row counts measured, the picks made from these tables take 0.9 % longer
-// than the best launch of each; the picks made from the tables above took
-// 21 % longer (33 % up to 192 rows). Above 1024 rows the launches run several
-// rounds of the large tiles, which is what the tables above describe.
-constexpr int kFewPoints = 15;
-const float kFewKt[kFewPoints] = {8, 14, 16, 24, 28, 32, 37, 48, 56, 64, 74, 96, 148, 192, 296};
-struct FewRowTable {
-  int cfg, occ;
-  float us1[kFewPoints], us2[kFewPoints];
+// Launches of up to kFewRows (kernels.h) rows, mostly one round of blocks. Modelled
+// time of a launch of `units` blocks that walk kt k-tiles each:
+//   4.3 + sqrt(walk^2 + stream^2) + output bytes / 6.46 TB/s       (us), with
+//   walk   = kt x rounds x us_kt, 27 % less where a tile holds no rows and 9 % less
+//            where no blocks run (in proportion),
+//   stream = the weights at 7.11 TB/s,
+// both 5 % longer where the row tiles walk weight rows a power of two apart from
+// the same k-tile (every block in step then reads the same HBM channels; the
+// four-stage tiles with one row tile start each column tile elsewhere), and the
+// consumer's reads of the extra K slices, 0.08 us + 0.25 a slice + 7.65 TB/s, with
+// 0.03 us a MB for slices beyond the 32 MB of the L2s; within 1 % the fewer slices,
+// which need less workspace.
+// rounds: whole ones, also a last partly filled one, which in quarter (half) tiles
+// counts 0.55 (0.75); 6 % more for five or more row tiles over two rounds or more
+// (28672 x 4096 at 800 to 960 rows: 192 x 256 tiles 195-203 us, 256 x 256 175-186). Of configurations that fit twice on a CU
+// (64 or 80 KB of LDS) a round of two blocks takes 1.6 times that of one, a last
+// partly filled one at least 0.75 of it.
+// The constants are fitted to the choice, not to the times: they minimise what the
+// chosen plans took over 2300 shapes and row counts (18000 launches inside steps,
+// MI355X, weights streamed from HBM; eight model shapes of 2048 to 8192 wide, 4 to
+// 1024 rows, every projection with its consumer). Over those samples the chosen plans
+// take 0.4 % longer than the best measured for the repository's two bf16 models and
+// 0.8 to 2 % for the others; single launches are up to 10 % off. Tables of
+// times by k-tile count, measured for the two models alone, chose as well for
+// them and up to 28 % worse elsewhere (2048 x 2048 at 512 to 1024 rows, 15.9 / 19.6
+// to 20.6 / 26.3 us).
+struct FewRowTile {
+  int cfg;
+  float us_kt;
+  int occ = 1;             // blocks that fit on a CU
 };
-const FewRowTable kFewRowTables[] = {
-    {80, 2, {5.0f, 7.9f, 9.2f, 11.1f, 12.0f, 13.4f, 15.5f, 20.2f, 20.1f, 22.3f, 27.6f, 34.3f, 48.7f, 59.3f, 88.6f},
-     {9.3f, 11.7f, 12.6f, 21.1f, 17.9f, 20.2f, 28.7f, 31.7f, 25.7f, 36.3f, 45.8f, 41.7f, 82.6f, 76.5f, 111.9f}},
-    {81, 1, {5.9f, 9.3f, 10.1f, 13.3f, 14.9f, 19.3f, 20.5f, 23.2f, 25.2f, 30.2f, 32.4f, 42.1f, 63.5f, 79.3f, 115.1f}, {}},
-    {82, 1, {9.8f, 12.2f, 11.6f, 21.2f, 16.2f, 18.3f, 25.7f, 27.6f, 26.6f, 30.8f, 44.5f, 46.3f, 67.3f, 84.4f, 125.0f}, {}},
-    {83, 1, {9.4f, 13.5f, 14.5f, 21.5f, 20.2f, 20.7f, 26.6f, 35.0f, 38.6f, 39.2f, 47.4f, 56.2f, 99.0f, 100.9f, 183.2f}, {}},
-    {84, 1, {7.0f, 10.9f, 11.8f, 14.7f, 16.2f, 18.3f, 21.3f, 28.0f, 28.0f, 31.7f, 38.2f, 45.7f, 66.4f, 87.1f, 125.6f}, {}},
-    {85, 1, {10.8f, 13.0f, 12.9f, 23.1f, 18.0f, 21.1f, 28.2f, 29.6f, 29.2f, 33.3f, 46.6f, 51.0f, 73.6f, 91.2f, 132.3f}, {}},
-    {86, 1, {11.2f, 15.3f, 16.0f, 24.5f, 24.4f, 25.6f, 31.2f, 37.0f, 41.8f, 41.8f, 49.9f, 67.5f, 99.3f, 108.1f, 176.1f}, {}},
-    {87, 1, {7.8f, 12.2f, 13.0f, 16.4f, 18.1f, 20.9f, 24.0f, 30.8f, 32.0f, 36.3f, 41.6f, 50.1f, 74.9f, 102.0f, 149.9f}, {}},
-    {88, 1, {12.5f, 15.4f, 15.9f, 25.2f, 22.5f, 25.2f, 31.2f, 35.6f, 37.8f, 42.3f, 50.8f, 63.8f, 92.4f, 115.1f, 173.5f}, {}},
-    {89, 1, {13.6f, 16.4f, 17.7f, 26.5f, 24.4f, 27.0f, 33.3f, 39.4f, 40.1f, 45.8f, 55.8f, 68.8f, 101.1f, 123.1f, 184.9f}, {}},
-    {90, 1, {13.8f, 18.5f, 19.5f, 28.0f, 28.3f, 30.1f, 36.3f, 43.2f, 54.8f, 52.5f, 60.4f, 76.5f, 118.0f, 135.0f, 203.9f}, {}},
-    {92, 1, {16.7f, 17.5f, 21.0f, 28.4f, 25.4f, 27.7f, 35.3f, 41.8f, 38.9f, 48.2f, 59.5f, 68.9f, 98.1f, 115.6f, 169.2f}, {}},
-    {93, 1, {15.3f, 20.5f, 33.3f, 30.6f, 31.5f, 37.0f, 39.3f, 48.7f, 60.9f, 65.7f, 70.4f, 87.8f, 131.2f, 170.2f, 262.3f}, {}},
-    {29, 1, {18.4f, 19.9f, 24.0f, 31.7f, 29.5f, 32.3f, 39.3f, 50.1f, 53.2f, 56.3f, 71.4f, 83.2f, 120.9f, 156.9f, 241.9f}, {}},
-    {21, 1, {18.0f, 24.7f, 30.2f, 36.8f, 39.1f, 45.9f, 49.0f, 61.6f, 71.5f, 79.7f, 89.5f, 116.6f, 169.0f, 219.3f, 338.0f}, {}},
-    {70, 1, {19.4f, 28.7f, 30.9f, 39.5f, 45.7f, 50.6f, 65.2f, 69.6f, 77.2f, 84.8f, 106.1f, 125.4f, 193.3f, 250.7f, 386.6f}, {}},
-    {6, 1, {24.9f, 31.9f, 33.0f, 49.2f, 50.8f, 52.4f, 67.1f, 73.8f, 83.7f, 93.7f, 110.0f, 142.8f, 220.1f, 285.5f, 440.2f}, {}},
+const FewRowTile kFewRowTiles[] = {
+    {80, 0.279f, 2}, {81, 0.357f, 2}, {82, 0.614f}, {83, 0.569f}, {84, 0.403f}, {85, 0.455f},
+    {86, 0.640f}, {87, 0.520f}, {88, 0.617f}, {89, 0.652f}, {90, 0.778f}, {92, 0.678f},
+    {93, 0.873f}, {22, 0.839f, 2}, {29, 0.807f}, {21, 1.163f}, {70, 1.266f}, {6, 1.378f},
 };
 
-// linear in k-tiles between the points, proportional outside them
-double interp_us(const float* kts, const float* us, int n, double kt) {
-  if (kt <= kts[0]) return us[0] * kt / kts[0];
-  for (int i = 1; i < n; ++i)
-    if (kt <= kts[i]) {
-      const double w = (kt - kts[i - 1]) / (kts[i] - kts[i - 1]);
-      return us[i - 1] + w * (us[i] - us[i - 1]);
-    }
-  return us[n - 1] * kt / kts[n - 1];
-}
-
-// Modelled time of `units` blocks of kt k-tiles: whole rounds of one block (two
-// for occ 2) per CU; a partly filled round costs a whole one if it is the only
-// one and at least 0.85 of one after others (its blocks start as the round
-// before drains; 0.75 to 1 pick equally well).
-double few_rows_us(const FewRowTable& t, double kt, long units, int num_cu) {
-  const double a = interp_us(kFewKt, t.us1, kFewPoints, kt);
-  if (t.occ == 2) {
-    const double b = interp_us(kFewKt, t.us2, kFewPoints, kt);
-    const long full = units / (2L * num_cu), rem = units - full * 2L * num_cu;
-    return full * b + (rem == 0 ? 0.0 : (rem <= num_cu && full == 0 ? a : b));
-  }
+double few_rows_us(const FewRowTile& t, int bm, long units, int sub, int M, int N, int K, int s,
+                   double out_mb, int num_cu) {
+  const int n_m = ceil_div(M, bm);
   const long full = units / num_cu, rem = units - full * num_cu;
-  if (rem == 0) return full * a;
-  return full == 0 ? a : (full + std::max(0.85, (double)rem / num_cu)) * a;
+  const double per_cu = (double)units / num_cu;
+  double rounds = (double)full;
+  if (t.occ == 2) {
+    const long pairs = units / (2L * num_cu), last = units - pairs * 2L * num_cu;
+    rounds = pairs + (last == 0 ? 0.0 : pairs ? std::max(0.75, last / (2.0 * num_cu)) : 1.0);
+    rounds = units <= num_cu ? 1.0 : 1.6 * rounds;
+  } else {
+    rounds += sub == 4 ? 0.55 : sub == 2 ? 0.75 : rem ? 1.0 : 0.0;
+    if (n_m >= 5 && full >= 2) rounds *= 1.06;
+  }
+  const bool in_step = (K & (K - 1)) == 0 && K >= 2048 && !(n_m == 1 && gemm_dl_stages(t.cfg) == 4);
+  const double f = in_step ? 1.0 + 0.054 / n_m : 1.0;
+  const double walk = (double)(K / 64 / s) * rounds * t.us_kt * f *
+                      (1.0 - 0.27 * (1.0 - (double)M / ((double)n_m * bm))) *
+                      (1.0 - 0.093 * (1.0 - std::min(1.0, per_cu)));
+  const double stream = (double)N * K * 2e-6 / 7.11 * f;
+  const double us = 4.29 + std::sqrt(walk * walk + stream * stream) + out_mb / 6.46;
+  if (s == 1) return us;
+  const double mb = (double)M * N * 4e-6;   // of a slice
+  return 1.01 * (us + mb * (s - 1) / 7.65 + 0.079 + 0.251 * (s - 1) +
+                 0.03 * std::max(0.0, mb * s - 32.0));
 }
 
-double round_us(const RoundTable& t, double kt) { return interp_us(t.kt, t.us, t.n, kt); }
+double round_us(const RoundTable& t, double kt) {
+  if (kt <= t.kt[0]) return t.us[0] * kt / t.kt[0];
+  for (int i = 1; i < t.n; ++i)
+    if (kt <= t.kt[i]) {
+      const double w = (kt - t.kt[i - 1]) / (t.kt[i] - t.kt[i - 1]);
+      return t.us[i - 1] + w * (t.us[i] - t.us[i - 1]);
+    }
+  return t.us[t.n - 1] * kt / t.kt[t.n - 1];
+}
+
+// Sub-tiles (0, 2 or 4 per tile) of a last round of rem tiles: quarters where they
+// fill a quarter of the CUs at most, halves at a half, as the configuration allows.
+int last_round_subs(int cfg, long rem, long slots) {
+  const int subs = gemm_dl_subs(cfg);
+  if (rem <= 0) return 0;
+  if ((subs & 4) && 4 * rem <= slots) return 4;
+  return (subs & 2) && 2 * rem <= slots ? 2 : 0;
+}
 }  // namespace
 
 GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, bool allow_mf32,
@@ -399,45 +417,25 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
     }
     return best;
   }
-  // time of the consumer's reads of the extra fp32 slices of a K split: few
-  // rows' slices come out of the caches (256 and 512 rows: 8 instead of 4
-  // slices cost the residual norm 1.7 us of 17 MB, 4 instead of 2 the RoPE
-  // kernel 4 us of 25 MB and the norm 1.5 us of 17 MB)
-  auto slice_us = [&](int s) {
-    return s > 1 ? (double)M * N * 4.0 * (s - 1) / (M <= few_rows ? 8.0e12 : 5.0e12) * 1e6 : 0.0;
-  };
-  long best_units = 0;
-  const bool streams = (double)N * K * es > 256e6;   // weights larger than the last-level cache
   double best_t = 1e30;
   if (M <= few_rows) {
-    for (const FewRowTable& c : kFewRowTables) {
+    for (const FewRowTile& c : kFewRowTiles) {
       if (!allow_odd && gemm_dl_odd(c.cfg)) continue;
       int bm, bn, th;
       gemm_dl_tile(c.cfg, &bm, &bn, &th);
-      // the small tiles reread the weights once per row tile: up to three
-      // (512 x 4096 x 4096 inside a step: 128x128 tiles 29.6 us and 256x128
-      // 23.6 us, 27 and 24 us alone with the activations in cache)
-      if (bm < 192 && ceil_div(M, bm) > 3) continue;
+      if (bm < 192 && ceil_div(M, bm) > 5) continue;   // (the weights once per row tile)
       for (int s = 1; s <= 8; s *= 2) {
-        if (s > 1 && (!splittable || (K / 64) % s != 0 || K / s < 512)) continue;
-        const long units = (long)ceil_div(M, bm) * ceil_div(N, bn) * s;
-        const double t = few_rows_us(c, (double)(K / s) / 64.0, units, num_cu) + slice_us(s);
+        if (s > 1 && (!splittable || c.cfg == 22 || (K / 64) % s != 0 || K / s < 512)) continue;
+        const long units = (long)ceil_div(M, bm) * ceil_div(N, bn) * s, rem = units % num_cu;
+        const int sub = allow_tail && c.occ == 1 ? last_round_subs(c.cfg, rem, num_cu) : 0;
+        // the gate/up launch (not splittable) stores half as many columns in bf16
+        const double out_mb = (double)M * N * (splittable ? 4e-6 * s : 1e-6);
+        const double t = few_rows_us(c, bm, units, sub, M, N, K, s, out_mb, num_cu);
         if (t < best_t * 0.999) {
           best_t = t;
-          best = GemmPlan{c.cfg, s, 0};
-          best_units = units;
+          best = GemmPlan{c.cfg, s, 0, sub, sub ? (int)rem : 0};
         }
       }
-    }
-    // Streaming weights in several rounds of which the last is not nearly full: the
-    // tables below, which split the last round of large tiles (GQA gate/up 37888x3584:
-    // 384 rows 131 -> 125 us, 512 136 -> 132, 560 170 -> 156, 960 253 -> 224; 300
-    // rows, two rounds to 0.93, stay: 95.7 us against 118.6). Weights that fit the
-    // cache stay too (MHA gate/up 24576x4096, 560 rows, 1.5 rounds: 115 against 138).
-    const long rem = best_units % num_cu;
-    if (streams && best_units > num_cu && rem != 0 && rem < 0.8 * num_cu) {
-      few_rows = 0;
-      best_t = 1e30;
     }
   }
   for (const RoundTable& c : kRoundTables) {
@@ -455,23 +453,14 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
       const long full = units / slots;
       const long rem = units - full * slots;
       const double fill = (double)rem / slots;
-      const int subs = allow_tail && c.occ == 1 ? gemm_dl_subs(c.cfg) : 0;
+      const int sub = allow_tail && c.occ == 1 ? last_round_subs(c.cfg, rem, slots) : 0;
       double rounds = (double)full;
-      int sub = 0;
-      if (rem > 0) {
-        if (c.occ > 1) {
-          rounds += std::max(0.7, fill);
-        } else if ((subs & 4) && 4 * rem <= slots) {
-          rounds += 0.55;
-          sub = 4;
-        } else if ((subs & 2) && 2 * rem <= slots) {
-          rounds += 0.75;
-          sub = 2;
-        } else {
-          rounds += 1.0;
-        }
-      }
-      const double t = rounds * round_us(c, (double)(K / s) / 64.0) + slice_us(s);
+      if (sub)
+        rounds += sub == 4 ? 0.55 : 0.75;
+      else if (rem > 0)
+        rounds += c.occ > 1 ? std::max(0.7, fill) : 1.0;
+      double t = rounds * round_us(c, (double)(K / s) / 64.0);
+      if (s > 1) t += (double)M * N * 4.0 * (s - 1) / 5.0e12 * 1e6;   // the consumer's reads
       if (t < best_t * 0.999) {
         best_t = t;
         best = GemmPlan{c.cfg, s, 0, sub, sub ? (int)rem : 0};
@@ -482,7 +471,7 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   // from HBM once per row tile in plain order: use the grouped XCD order
   int bm, bn, th;
   if (best.cfg >= 0 && gemm_dl_tile(best.cfg, &bm, &bn, &th) && ceil_div(M, bm) > 1 &&
-      streams)
+      (double)N * K * es > 256e6)
     best.group_m = 8;
   return best;
 }
@@ -495,9 +484,8 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
 // 5.8 TB/s).
 GemmPlan lm_head_plan(int es, int M, int V, int K, int num_cu) {
   // the head's epilogue is 16x16 and keeps whole tiles (its partial results are per column tile)
-  // It also runs many rounds at any row count, so the few-row tables (one
-  // round) do not describe it: their picks took 5-8 % longer at 65 to 128
-  // rows (100 rows, MHA 200 us against 210, GQA 234 against 248).
+  // It also runs many rounds at any row count, so the few-row model (one
+  // round) does not describe it.
   GemmPlan p = gemm_plan(es, M, V, K, false, num_cu, false, false, false, 0, false);
   if (p.cfg >= 0 && M <= 64) p = GemmPlan{((long)K * es) % 8192 == 0 ? 11 : 10, 1, 0};
   // The head is planned for its largest row count and skips, on the device,

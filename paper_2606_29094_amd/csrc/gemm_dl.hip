@@ -758,6 +758,17 @@ int gemm_dl_odd(int cfg) {
   return 0;
 }
 
+// Activation stages (the four-stage tiles can rotate their K walk).
+int gemm_dl_stages(int cfg) {
+  switch (cfg) {
+#define X(id, BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_) \
+  case id: return SA_;
+    DL_CONFIGS(X)
+#undef X
+  }
+  return 0;
+}
+
 // Sub-tile splits a configuration allows for the last round (bit 1: halves,
 // bit 2: quarters).
 int gemm_dl_subs(int cfg) {

@@ -96,6 +96,7 @@ int gemm_dl_tile(int cfg, int* bm, int* bn, int* threads);
 int gemm_dl_mfma(int cfg);
 int gemm_dl_subs(int cfg);
 int gemm_dl_odd(int cfg);
+int gemm_dl_stages(int cfg);
 // one launch of configuration cfg with epilogue 0 (fp32 store of `splits` K
 // slices), 1 (SwiGLU to bf16, N = 2 F) or 2 (fp32 add), A [M, K], B [N, K],
 // C row-major (test hook)
@@ -105,7 +106,7 @@ hipError_t gemm_debug_launch(int cfg, int epilogue, int sub, int n_tail, int gro
 // allow_tail: the last round may be split into sub-tiles (epilogues that allow it)
 // allow_odd: configurations whose wave tiles hold an odd number of column
 // fragments may be chosen (every epilogue but SwiGLU)
-// few_rows: launches of up to that many rows are planned from the few-row tables
+// few_rows: launches of up to that many rows are planned by the few-row model
 constexpr int kFewRows = 1024;
 // allow_small: fp32 launches whose 128-wide tiles would not fill the CUs may use
 // the 16x32-tile kernel (plan cfg kSmallF32; every epilogue that needs only its

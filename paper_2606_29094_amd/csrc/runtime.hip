@@ -186,18 +186,25 @@ struct Layout {
   int s_qkv, s_o, s_down, tiles, m_max;
 };
 
+GemmPlan projection_plan(int es, int rows, int N, int K, int num_cu) {
+  return gemm_plan(es, rows, N, K, true, num_cu);
+}
+// the SwiGLU GEMM keeps 16x16 tiles: its 32x32 variants measured 5-6 % slower on
+// every gate/up shape
+GemmPlan gate_up_plan(int es, int rows, int F, int K, int num_cu) {
+  return gemm_plan(es, rows, 2 * F, K, false, num_cu, false, true, false);
+}
+
 Layout layout(const dlm_model* m, int n, int n_req) {
   const dlm_config& c = m->cfg;
   Layout L{};
   const int qkv_dim = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
   const int qd = c.n_q_heads * c.head_dim;
   const int es_i = (int)m->es;
-  L.g_qkv = gemm_plan(es_i, n, qkv_dim, c.d_model, true, m->num_cu);
-  L.g_o = gemm_plan(es_i, n, c.d_model, qd, true, m->num_cu);
-  // the SwiGLU GEMM keeps 16x16 tiles: its 32x32 variants measured 5-6 %
-  // slower on every gate/up shape
-  L.g_gu = gemm_plan(es_i, n, 2 * c.d_ffn, c.d_model, false, m->num_cu, false, true, false);
-  L.g_down = gemm_plan(es_i, n, c.d_model, c.d_ffn, true, m->num_cu);
+  L.g_qkv = projection_plan(es_i, n, qkv_dim, c.d_model, m->num_cu);
+  L.g_o = projection_plan(es_i, n, c.d_model, qd, m->num_cu);
+  L.g_gu = gate_up_plan(es_i, n, c.d_ffn, c.d_model, m->num_cu);
+  L.g_down = projection_plan(es_i, n, c.d_model, c.d_ffn, m->num_cu);
   L.m_max = std::min(n, n_req * kMaxBlock);
   L.g_lm = lm_head_plan(es_i, L.m_max, c.vocab, c.d_model, m->num_cu);
   L.g_logits = L.g_lm;
@@ -801,6 +808,24 @@ dlm_status dlm_head_confidence(dlm_model* m, const void* u_rows, int32_t m_rows,
                                  cf.d_model, cf.inv_tau, pm, ps, pi, m_rows, nullptr, st));
   }
   HIPCHECK(lm_combine(pm, ps, pi, tiles, m_rows, nullptr, m_rows, conf, tok, st));
+  return DLM_OK;
+}
+
+dlm_status dlm_debug_gemm_plan(int32_t elem_bytes, int32_t M, int32_t N, int32_t K, int32_t kind,
+                               int32_t num_cu, int32_t out[4]) {
+  g_err.clear();
+  if (!out) return fail(DLM_EINVAL, "out is NULL");
+  if ((elem_bytes != 2 && elem_bytes != 4) || M < 1 || N < 1 || K < 1 || num_cu < 1 || kind < 0 ||
+      kind > 2 || (kind == 1 && N % 2 != 0))
+    return fail(DLM_EINVAL, "elem_bytes %d, M %d N %d K %d, kind %d, %d CUs", elem_bytes, M, N, K,
+                kind, num_cu);
+  const GemmPlan p = kind == 0   ? projection_plan(elem_bytes, M, N, K, num_cu)
+                     : kind == 1 ? gate_up_plan(elem_bytes, M, N / 2, K, num_cu)
+                                 : lm_head_plan(elem_bytes, M, N, K, num_cu);
+  out[0] = p.cfg;
+  out[1] = p.splits;
+  out[2] = p.sub;
+  out[3] = p.n_tail;
   return DLM_OK;
 }
 

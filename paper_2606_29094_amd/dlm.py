@@ -27,7 +27,7 @@ EXPORTS = ["dlm_load_weights", "dlm_model_destroy", "dlm_workspace_bytes",
            "dlm_kv_cache_alloc", "dlm_cache_destroy", "dlm_cache_invalidate",
            "dlm_denoise_step", "dlm_denoise_step_noalloc", "dlm_cache_refresh",
            "dlm_debug_logits", "dlm_debug_trace", "dlm_debug_gemm_info", "dlm_debug_gemm",
-           "dlm_debug_attention_plan",
+           "dlm_debug_gemm_plan", "dlm_debug_attention_plan",
            "dlm_head_confidence", "dlm_profile_enable", "dlm_profile_read",
            "dlm_profile_sample", "dlm_ceiling_mfma", "dlm_ceiling_copy", "dlm_last_error"]
 
@@ -125,6 +125,8 @@ def lib():
         L.dlm_debug_gemm.argtypes = [c_int32, c_int32, c_int32, c_int32, c_int32, c_int32,
                                      c_void_p, c_void_p, c_void_p, c_int32, c_int32, c_int32,
                                      c_void_p]
+        L.dlm_debug_gemm_plan.argtypes = [c_int32, c_int32, c_int32, c_int32, c_int32, c_int32,
+                                          POINTER(c_int32)]
         L.dlm_debug_attention_plan.argtypes = [c_int32, c_int32, c_int32, c_int32,
                                                POINTER(c_int32), POINTER(c_int32), c_size_t,
                                                c_int32, POINTER(c_int32), POINTER(c_int32)]
@@ -141,8 +143,8 @@ def lib():
                      "dlm_cache_invalidate", "dlm_denoise_step", "dlm_denoise_step_noalloc",
                      "dlm_cache_refresh",
                      "dlm_debug_logits", "dlm_debug_trace", "dlm_head_confidence",
-                     "dlm_debug_gemm_info", "dlm_debug_gemm", "dlm_debug_attention_plan",
-                     "dlm_profile_enable",
+                     "dlm_debug_gemm_info", "dlm_debug_gemm", "dlm_debug_gemm_plan",
+                     "dlm_debug_attention_plan", "dlm_profile_enable",
                      "dlm_profile_read", "dlm_profile_sample"]:
             getattr(L, name).restype = c_int32
         _lib = L
@@ -277,6 +279,15 @@ def debug_gemm_info(cfg: int):
     if rc != DLM_OK:
         return None
     return bm.value, bn.value, subs.value
+
+
+def debug_gemm_plan(M: int, N: int, K: int, kind: int = 0, elem_bytes: int = 2,
+                    num_cu: int = 256):
+    """(configuration, K slices, sub-tiles, tiles run as them) of a GEMM launch
+    (dlm_debug_gemm_plan)."""
+    out = (c_int32 * 4)()
+    check(lib().dlm_debug_gemm_plan(elem_bytes, M, N, K, kind, num_cu, out))
+    return tuple(out)
 
 
 def debug_attention_plan(hq: int, hkv: int, dh: int, rows, lens, scratch_bytes: int,

@@ -64,3 +64,56 @@ def test_attention_plan_of_a_smaller_chip():
     for n in (4, 5, 8, 9):
         assert dlm.debug_attention_plan(*MHA, [32] * n, [1280] * n, 0, 128) == \
             dlm.debug_attention_plan(*MHA, [32] * 2 * n, [1280] * 2 * n, 0, 256)
+
+
+def _tile(cfg):
+    return dlm.debug_gemm_info(cfg)[:2]
+
+
+PROJECTION, GATE_UP, HEAD = range(3)
+SHAPES = [(12288, 4096, 0), (4096, 4096, 0), (24576, 4096, 1), (4096, 12288, 0),
+          (4608, 3584, 0), (3584, 3584, 0), (37888, 3584, 1), (3584, 18944, 0),
+          (2048, 2048, 0), (57344, 8192, 1), (192, 128, 0), (128, 192, 0), (3072, 1536, 1)]
+
+
+@pytest.mark.parametrize("rows", [1, 32, 64])
+def test_few_rows_take_short_tiles(rows):
+    # a weight that streams in many rounds of blocks as well: 64-row tiles 164 to 184 us
+    # of a 57344 x 8192 launch, 128-row tiles 179 to 224
+    for N, K, kind in SHAPES:
+        cfg = dlm.debug_gemm_plan(rows, N, K, kind)[0]
+        assert _tile(cfg)[0] <= 96, (rows, N, K, cfg)
+
+
+def test_projection_plans_against_measured_launches():
+    # (rows, N, K) -> plans within 5 % of the best measured with its consumer, at sizes
+    # where tables of one round's times by k-tile count were 7 to 28 % off
+    for (M, N, K), good in {(512, 2048, 2048): [(89, 4), (87, 2), (29, 2), (84, 2), (85, 2)],
+                            (896, 2048, 2048): [(29, 2)],
+                            (240, 7168, 5120): [(29, 4), (92, 2), (89, 2), (93, 4)],
+                            (640, 5120, 5120): [(90, 2), (29, 2)],
+                            (900, 5120, 13824): [(21, 2)],
+                            (224, 12288, 4096): [(93, 2), (87, 1), (21, 4)],
+                            (230, 3584, 3584): [(29, 4), (82, 2), (88, 4)]}.items():
+        assert dlm.debug_gemm_plan(M, N, K)[:2] in good, (M, N, K, dlm.debug_gemm_plan(M, N, K))
+
+
+@pytest.mark.parametrize("N,K,kind", SHAPES)
+def test_every_plan_can_be_launched(N, K, kind):
+    for num_cu in (256, 64):
+        for M in list(range(1, 66)) + list(range(96, 1100, 13)) + [1024, 1025, 4096, 65536]:
+            cfg, s, sub, tail = dlm.debug_gemm_plan(M, N, K, kind, 2, num_cu)
+            bm, bn, flags = dlm.debug_gemm_info(cfg)
+            assert s >= 1 and (K // 64) % s == 0 and (s == 1 or kind == PROJECTION)
+            assert kind != GATE_UP or not flags & 8          # whole gate/up pairs per wave
+            tiles = -(-M // bm) * -(-N // bn) * s
+            assert sub in (0, 2, 4) and (sub == 0 or flags & sub) and tail <= tiles
+            assert (sub == 0) == (tail == 0)
+
+
+@pytest.mark.parametrize("rows", [769, 800, 811])
+def test_near_ties_take_fewer_slices(rows):
+    """QKV 6144 x 4096: one slice of 192 x 128 tiles and two of 256 x 192 are within 1 % in
+    the model (45.2 and 44.5 us at 800 rows, the second's reader 2.6 us longer); two
+    slices would take the step of the 14336-wide model past the fixed scratch."""
+    assert dlm.debug_gemm_plan(rows, 6144, 4096, 0)[1] == 1
