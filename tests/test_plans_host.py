@@ -111,6 +111,14 @@ def test_every_plan_can_be_launched(N, K, kind):
             assert (sub == 0) == (tail == 0)
 
 
+@pytest.mark.parametrize("rows,N,K,kind,small", [
+    (1280, 1408, 256, 1, True), (2048, 1408, 256, 1, False), (2816, 1408, 256, 1, False),
+    (2560, 768, 256, 0, True), (3840, 768, 256, 0, False), (5120, 256, 704, 0, True),
+    (1, 704, 256, 0, True), (64, 4096, 1088, 0, False)])
+def test_small_fp32_tiles_only_where_half_of_the_chip_idles(rows, N, K, kind, small):
+    assert (dlm.debug_gemm_plan(rows, N, K, kind, elem_bytes=4)[0] == -2) == small
+
+
 @pytest.mark.parametrize("rows", [769, 800, 811])
 def test_near_ties_take_fewer_slices(rows):
     """QKV 6144 x 4096: one slice of 192 x 128 tiles and two of 256 x 192 are within 1 % in
