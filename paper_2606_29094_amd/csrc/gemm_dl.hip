@@ -5,10 +5,11 @@
 // of that kilobyte, and it fetches the global 16-byte chunk that belongs
 // there under an XOR swizzle (LDS chunk slot = global chunk ^ swz(row)), so
 // that the lanes that later read consecutive rows of one chunk hit distinct
-// banks. The weight operand B goes SB-1 k-tiles ahead through a ring of SB LDS
-// stages and the activation operand A one k-tile ahead through two (A is
-// re-read by every column tile and mostly served from cache; B streams from
-// HBM and needs the deeper prefetch); no registers hold tiles in flight.
+// banks. The operands go SA-1 (activations A) and SB-1 (weights B) k-tiles
+// ahead through rings of SA and SB LDS stages, SB >= SA (A is re-read by every
+// column tile and mostly served from cache; B streams from HBM and needs the
+// deeper prefetch; the few-row tiles run both three ahead or two); no registers
+// hold tiles in flight.
 // Waves multiply with v_mfma_f32_16x16x32_bf16 (MF = 16) or
 // v_mfma_f32_32x32x16_bf16 (MF = 32); the 16x16 epilogues are the same as the
 // register-staged kernel's, the 32x32 ones (plain, residual-add and SwiGLU
