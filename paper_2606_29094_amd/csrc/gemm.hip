@@ -403,7 +403,7 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   if (es != 2 || K % 64 != 0) {
     const int bm = M <= 32 ? 32 : (M <= 64 ? 64 : 128);
     const long tiles = (long)ceil_div(N, 128) * ceil_div(M, bm);
-    // Small tiles where the staged kernel's leave half of the CUs idle. 1408 x 256 at
+    // Small tiles where the staged kernel's leave half of the CUs idle. 1376 x 256 at
     // 1280, 1536 and 2048 rows (110, 132 and 176 staged tiles): staged 24.9, 25.4 and
     // 26.2 us, small 22.0, 25.7 and 31.7; 768 x 256 at 3072 and 3840 rows (144 and 180)
     // 26.5 and 27.3 against 26.7 and 33.2; 256 x 256 at 5120 (80) 33.2 against 21.1.
