@@ -53,6 +53,7 @@ struct EpiStore {
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
   static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
+  static constexpr bool kHead = false;
   __host__ __device__ void set_mfma(int) {}
   __device__ int b_row(int n) const { return n; }
   __device__ bool skip_tile(int) const { return false; }
@@ -99,6 +100,7 @@ struct EpiScaledStore {
   static constexpr bool kTailSplit = false;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
   static constexpr bool kWaveLocal = false;
+  static constexpr bool kHead = true;   // launched with the head's tiles only
   __host__ __device__ void set_mfma(int) {}
   template <int FM, int FN>
   __device__ void op32(f32x16 (&)[FM][FN], int, int, int, int) const {}
@@ -132,6 +134,7 @@ struct EpiAdd {
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
   static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
+  static constexpr bool kHead = false;
   __host__ __device__ void set_mfma(int) {}
   __device__ int b_row(int n) const { return n; }
   __device__ bool skip_tile(int) const { return false; }
@@ -206,6 +209,7 @@ struct EpiSwiGLU {
   }
   __device__ bool skip_tile(int) const { return false; }
   static constexpr bool kWaveLocal = true;   // the epilogue needs no other wave of the block
+  static constexpr bool kHead = false;
   static constexpr bool kRotateK = false;
   static constexpr bool kMf32 = true;
   static constexpr bool kTailSplit = true;   // last-round tiles may be split
@@ -287,6 +291,7 @@ struct EpiLMHead {
   static constexpr bool kTailSplit = false;   // last-round tiles may be split
   static constexpr bool kOddFragments = true;   // any number of 16-column fragments per wave
   static constexpr bool kWaveLocal = false;
+  static constexpr bool kHead = true;   // launched with the head's tiles only
   __host__ __device__ void set_mfma(int) {}
   template <int FM, int FN>
   __device__ void op32(f32x16 (&)[FM][FN], int, int, int, int) const {}

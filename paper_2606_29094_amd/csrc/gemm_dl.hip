@@ -727,6 +727,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_dl_head_kernel(
   X(92, 192, 128, 4, 2, 3, 3, 128, 16, 1)  \
   X(93, 192, 192, 4, 2, 3, 3, 128, 16, 1)
 
+// The configurations lm_head_plan chooses from (16x16 MFMA, an even number of column
+// fragments, many rounds); the head's and the logits' epilogues exist for these only.
+constexpr bool head_tile(int cfg) {
+  return cfg == 1 || cfg == 6 || cfg == 10 || cfg == 11 || cfg == 21 || cfg == 22 || cfg == 29 ||
+         cfg == 42;
+}
+
 int gemm_dl_tile(int cfg, int* bm, int* bn, int* threads) {
   switch (cfg) {
 #define X(id, BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_) \
@@ -801,7 +808,7 @@ hipError_t gemm_dl_launch(int cfg, const bf16* A, int lda, const bf16* B, int ld
   switch (cfg) {
 #define X(id, BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_)                                        \
   case id: {                                                                             \
-    if constexpr ((MF_ == 32 && !Epi::kMf32) ||                                          \
+    if constexpr ((MF_ == 32 && !Epi::kMf32) || (Epi::kHead && !head_tile(id)) ||        \
                   (!Epi::kOddFragments && (BN_ / WN_ / MF_) % 2 != 0))                   \
       return hipErrorInvalidValue;                                                       \
     else {                                                                               \
@@ -845,7 +852,7 @@ hipError_t gemm_dl_head_launch(int cfg, const bf16* A, int lda, const bf16* B, i
   switch (cfg) {
 #define X(id, BM_, BN_, WM_, WN_, SA_, S_, RB_, MF_, SP_)                                         \
   case id: {                                                                              \
-    if constexpr (MF_ == 32) return hipErrorInvalidValue;                                 \
+    if constexpr (!head_tile(id)) return hipErrorInvalidValue;                            \
     else {                                                                                \
       /* blocks per CU: bounded by the LDS (160 KB) and by 32 waves per CU */              \
       constexpr int kLds = (SA_ * BM_ + S_ * BN_) * RB_, kWaves = WM_ * WN_;                     \

@@ -112,9 +112,9 @@ def test_every_plan_can_be_launched(N, K, kind):
 
 
 @pytest.mark.parametrize("rows,N,K,kind,small", [
-    (1280, 1408, 256, 1, True), (2048, 1408, 256, 1, False), (2816, 1408, 256, 1, False),
-    (2560, 768, 256, 0, True), (3840, 768, 256, 0, False), (5120, 256, 704, 0, True),
-    (1, 704, 256, 0, True), (64, 4096, 1088, 0, False)])
+    (1280, 1376, 256, 1, True), (2048, 1408, 256, 1, False), (2816, 1408, 256, 1, False),
+    (2560, 768, 256, 0, True), (3840, 768, 256, 0, False), (5120, 256, 688, 0, True),
+    (1, 688, 256, 0, True), (64, 4096, 1088, 0, False)])
 def test_small_fp32_tiles_only_where_half_of_the_chip_idles(rows, N, K, kind, small):
     assert (dlm.debug_gemm_plan(rows, N, K, kind, elem_bytes=4)[0] == -2) == small
 
@@ -125,3 +125,10 @@ def test_near_ties_take_fewer_slices(rows):
     the model (45.2 and 44.5 us at 800 rows, the second's reader 2.6 us longer); two
     slices would take the step of the 14336-wide model past the fixed scratch."""
     assert dlm.debug_gemm_plan(rows, 6144, 4096, 0)[1] == 1
+
+
+@pytest.mark.parametrize("vocab,d", [(126464, 4096), (152064, 3584), (32000, 2048), (2048, 256)])
+def test_head_plans_are_tiles_the_head_is_built_for(vocab, d):
+    """The head's and the logits' epilogues exist for these configurations alone."""
+    for rows in [*range(1, 1100, 7), 1400, 2048, 4096, 8192]:
+        assert dlm.debug_gemm_plan(rows, vocab, d, 2)[0] in (1, 6, 10, 11, 21, 22, 29, 42)
