@@ -349,8 +349,17 @@ const FewRowTile kFewRowTiles[] = {
     {93, 0.873f}, {22, 0.839f, 2}, {29, 0.807f}, {21, 1.163f}, {70, 1.266f}, {6, 1.378f},
 };
 
-double few_rows_us(const FewRowTile& t, int bm, long units, int sub, int M, int N, int K, int s,
-                   double out_mb, int num_cu) {
+// The parts that need no tile: fixed, output and slices (with the 1 %), in us.
+double few_rows_base_us(int M, int N, int s, bool gate_up) {
+  const double mb = (double)M * N * 4e-6;   // of a slice; gate/up stores half the columns in bf16
+  const double us = 4.29 + (gate_up ? 0.25 : (double)s) * mb / 6.46;
+  if (s == 1) return us;
+  return 1.01 * (us + mb * (s - 1) / 7.65 + 0.079 + 0.251 * (s - 1) +
+                 0.03 * std::max(0.0, mb * s - 32.0));
+}
+
+double few_rows_us(const FewRowTile& t, int bm, int stages, long units, int sub, int M, int N,
+                   int K, int s, int num_cu, double base) {
   const int n_m = ceil_div(M, bm);
   const long full = units / num_cu, rem = units - full * num_cu;
   const double per_cu = (double)units / num_cu;
@@ -363,17 +372,13 @@ double few_rows_us(const FewRowTile& t, int bm, long units, int sub, int M, int 
     rounds += sub == 4 ? 0.55 : sub == 2 ? 0.75 : rem ? 1.0 : 0.0;
     if (n_m >= 5 && full >= 2) rounds *= 1.06;
   }
-  const bool in_step = (K & (K - 1)) == 0 && K >= 2048 && !(n_m == 1 && gemm_dl_stages(t.cfg) == 4);
+  const bool in_step = (K & (K - 1)) == 0 && K >= 2048 && !(n_m == 1 && stages == 4);
   const double f = in_step ? 1.0 + 0.054 / n_m : 1.0;
   const double walk = (double)(K / 64 / s) * rounds * t.us_kt * f *
                       (1.0 - 0.27 * (1.0 - (double)M / ((double)n_m * bm))) *
                       (1.0 - 0.093 * (1.0 - std::min(1.0, per_cu)));
   const double stream = (double)N * K * 2e-6 / 7.11 * f;
-  const double us = 4.29 + std::sqrt(walk * walk + stream * stream) + out_mb / 6.46;
-  if (s == 1) return us;
-  const double mb = (double)M * N * 4e-6;   // of a slice
-  return 1.01 * (us + mb * (s - 1) / 7.65 + 0.079 + 0.251 * (s - 1) +
-                 0.03 * std::max(0.0, mb * s - 32.0));
+  return base + std::sqrt(walk * walk + stream * stream) * (s > 1 ? 1.01 : 1.0);
 }
 
 double round_us(const RoundTable& t, double kt) {
@@ -424,18 +429,22 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   }
   double best_t = 1e30;
   if (M <= few_rows) {
+    double base[9];
+    for (int sp = 1; sp <= 8; sp *= 2) base[sp] = few_rows_base_us(M, N, sp, !splittable);
+    const double stream = (double)N * K * 2e-6 / 7.11;
     for (const FewRowTile& c : kFewRowTiles) {
       if (!allow_odd && gemm_dl_odd(c.cfg)) continue;
       int bm, bn, th;
       gemm_dl_tile(c.cfg, &bm, &bn, &th);
       if (bm < 192 && ceil_div(M, bm) > 5) continue;   // (the weights once per row tile)
+      const int stages = gemm_dl_stages(c.cfg);
+      const long tiles = (long)ceil_div(M, bm) * ceil_div(N, bn);
       for (int s = 1; s <= 8; s *= 2) {
         if (s > 1 && (!splittable || c.cfg == 22 || (K / 64) % s != 0 || K / s < 512)) continue;
-        const long units = (long)ceil_div(M, bm) * ceil_div(N, bn) * s, rem = units % num_cu;
+        if (base[s] + stream >= best_t) break;   // (more slices only add to the base)
+        const long units = tiles * s, rem = units % num_cu;
         const int sub = allow_tail && c.occ == 1 ? last_round_subs(c.cfg, rem, num_cu) : 0;
-        // the gate/up launch (not splittable) stores half as many columns in bf16
-        const double out_mb = (double)M * N * (splittable ? 4e-6 * s : 1e-6);
-        const double t = few_rows_us(c, bm, units, sub, M, N, K, s, out_mb, num_cu);
+        const double t = few_rows_us(c, bm, stages, units, sub, M, N, K, s, num_cu, base[s]);
         if (t < best_t * 0.999) {
           best_t = t;
           best = GemmPlan{c.cfg, s, 0, sub, sub ? (int)rem : 0};
