@@ -326,9 +326,9 @@ const RoundTable kRoundTables[] = {
 // which need less workspace.
 // rounds: whole ones, also a last partly filled one, which in quarter (half) tiles
 // counts 0.55 (0.75); 6 % more for five or more row tiles over two rounds or more
-// (28672 x 4096 at 800 to 960 rows: 192 x 256 tiles 195-203 us, 256 x 256 175-186). Of configurations that fit twice on a CU
-// (64 or 80 KB of LDS) a round of two blocks takes 1.6 times that of one, a last
-// partly filled one at least 0.75 of it.
+// (28672 x 4096 at 800 to 960 rows: 192 x 192 tiles 195-203 us, 256 x 256 175-186).
+// Of configurations that fit twice on a CU (64 or 80 KB of LDS) a round of two blocks
+// takes 1.6 times that of one, a last partly filled one at least 0.75 of it.
 // The constants are fitted to the choice, not to the times: they minimise what the
 // chosen plans took over 2300 shapes and row counts (18000 launches inside steps,
 // MI355X, weights streamed from HBM; eight model shapes of 2048 to 8192 wide, 4 to
