@@ -358,27 +358,30 @@ double few_rows_base_us(int M, int N, int s, bool gate_up) {
                  0.03 * std::max(0.0, mb * s - 32.0));
 }
 
-double few_rows_us(const FewRowTile& t, int bm, int stages, long units, int sub, int M, int N,
-                   int K, int s, int num_cu, double base) {
-  const int n_m = ceil_div(M, bm);
-  const long full = units / num_cu, rem = units - full * num_cu;
-  const double per_cu = (double)units / num_cu;
-  double rounds = (double)full;
-  if (t.occ == 2) {
-    const long pairs = units / (2L * num_cu), last = units - pairs * 2L * num_cu;
-    rounds = pairs + (last == 0 ? 0.0 : pairs ? std::max(0.75, last / (2.0 * num_cu)) : 1.0);
-    rounds = units <= num_cu ? 1.0 : 1.6 * rounds;
-  } else {
-    rounds += sub == 4 ? 0.55 : sub == 2 ? 0.75 : rem ? 1.0 : 0.0;
-    if (n_m >= 5 && full >= 2) rounds *= 1.06;
-  }
-  const bool in_step = (K & (K - 1)) == 0 && K >= 2048 && !(n_m == 1 && stages == 4);
-  const double f = in_step ? 1.0 + 0.054 / n_m : 1.0;
-  const double walk = (double)(K / 64 / s) * rounds * t.us_kt * f *
-                      (1.0 - 0.27 * (1.0 - (double)M / ((double)n_m * bm))) *
-                      (1.0 - 0.093 * (1.0 - std::min(1.0, per_cu)));
-  const double stream = (double)N * K * 2e-6 / 7.11 * f;
-  return base + std::sqrt(walk * walk + stream * stream) * (s > 1 ? 1.01 : 1.0);
+// A tile of kFewRowTiles with its dimensions.
+struct FewRowDims {
+  int cfg, bm, bn, stages, subs, occ;
+  bool odd;
+  double us_kt;
+};
+constexpr int kFewRowCount = sizeof(kFewRowTiles) / sizeof(kFewRowTiles[0]);
+const FewRowDims* few_row_dims() {
+  struct Dims {
+    FewRowDims d[kFewRowCount];
+    Dims() {
+      for (int i = 0; i < kFewRowCount; ++i) {
+        const FewRowTile& t = kFewRowTiles[i];
+        FewRowDims& x = d[i];
+        int th;
+        gemm_dl_tile(t.cfg, &x.bm, &x.bn, &th);
+        x.cfg = t.cfg, x.us_kt = t.us_kt, x.occ = t.occ;
+        x.stages = gemm_dl_stages(t.cfg), x.odd = gemm_dl_odd(t.cfg) != 0;
+        x.subs = t.occ == 1 ? gemm_dl_subs(t.cfg) : 0;
+      }
+    }
+  };
+  static const Dims dims;
+  return dims.d;
 }
 
 double round_us(const RoundTable& t, double kt) {
@@ -393,8 +396,7 @@ double round_us(const RoundTable& t, double kt) {
 
 // Sub-tiles (0, 2 or 4 per tile) of a last round of rem tiles: quarters where they
 // fill a quarter of the CUs at most, halves at a half, as the configuration allows.
-int last_round_subs(int cfg, long rem, long slots) {
-  const int subs = gemm_dl_subs(cfg);
+int last_round_subs(int subs, long rem, long slots) {
   if (rem <= 0) return 0;
   if ((subs & 4) && 4 * rem <= slots) return 4;
   return (subs & 2) && 2 * rem <= slots ? 2 : 0;
@@ -431,20 +433,37 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
   if (M <= few_rows) {
     double base[9];
     for (int sp = 1; sp <= 8; sp *= 2) base[sp] = few_rows_base_us(M, N, sp, !splittable);
-    const double stream = (double)N * K * 2e-6 / 7.11;
-    for (const FewRowTile& c : kFewRowTiles) {
-      if (!allow_odd && gemm_dl_odd(c.cfg)) continue;
-      int bm, bn, th;
-      gemm_dl_tile(c.cfg, &bm, &bn, &th);
-      if (bm < 192 && ceil_div(M, bm) > 5) continue;   // (the weights once per row tile)
-      const int stages = gemm_dl_stages(c.cfg);
-      const long tiles = (long)ceil_div(M, bm) * ceil_div(N, bn);
+    const bool pow2 = (K & (K - 1)) == 0 && K >= 2048;
+    const double stream0 = (double)N * K * 2e-6 / 7.11, inv_cu = 1.0 / num_cu;
+    const FewRowDims* const tiles = few_row_dims();
+    for (int i = 0; i < kFewRowCount; ++i) {
+      const FewRowDims& c = tiles[i];
+      if (!allow_odd && c.odd) continue;
+      const int n_m = ceil_div(M, c.bm);
+      if (c.bm < 192 && n_m > 5) continue;   // (the weights once per row tile)
+      const double f = pow2 && !(n_m == 1 && c.stages == 4) ? 1.0 + 0.054 / n_m : 1.0;
+      const double stream = stream0 * f;
+      const double us_kt = c.us_kt * f * (1.0 - 0.27 * (1.0 - (double)M / ((double)n_m * c.bm)));
+      const long n_tiles = (long)n_m * ceil_div(N, c.bn);
       for (int s = 1; s <= 8; s *= 2) {
         if (s > 1 && (!splittable || c.cfg == 22 || (K / 64) % s != 0 || K / s < 512)) continue;
-        if (base[s] + stream >= best_t) break;   // (more slices only add to the base)
-        const long units = tiles * s, rem = units % num_cu;
-        const int sub = allow_tail && c.occ == 1 ? last_round_subs(c.cfg, rem, num_cu) : 0;
-        const double t = few_rows_us(c, bm, stages, units, sub, M, N, K, s, num_cu, base[s]);
+        const double scale = s > 1 ? 1.01 : 1.0;
+        if (base[s] + stream * scale >= best_t) break;   // (more slices only add to the base)
+        const long units = n_tiles * s, full = units / num_cu, rem = units - full * num_cu;
+        const int sub = allow_tail ? last_round_subs(c.subs, rem, num_cu) : 0;
+        double rounds = (double)full;
+        if (c.occ == 2) {
+          const long pairs = full / 2, last = units - pairs * 2 * num_cu;
+          rounds = pairs + (last == 0 ? 0.0 : pairs ? std::max(0.75, 0.5 * last * inv_cu) : 1.0);
+          rounds = units <= num_cu ? 1.0 : 1.6 * rounds;
+        } else {
+          rounds += sub == 4 ? 0.55 : sub == 2 ? 0.75 : rem ? 1.0 : 0.0;
+          if (n_m >= 5 && full >= 2) rounds *= 1.06;
+        }
+        const double walk = (K / 64 / s) * rounds * us_kt *
+                            (1.0 - 0.093 * (1.0 - std::min(1.0, units * inv_cu)));
+        if (base[s] + walk * scale >= best_t) continue;
+        const double t = base[s] + std::sqrt(walk * walk + stream * stream) * scale;
         if (t < best_t * 0.999) {
           best_t = t;
           best = GemmPlan{c.cfg, s, 0, sub, sub ? (int)rem : 0};
@@ -467,7 +486,7 @@ GemmPlan gemm_plan(int es, int M, int N, int K, bool splittable, int num_cu, boo
       const long full = units / slots;
       const long rem = units - full * slots;
       const double fill = (double)rem / slots;
-      const int sub = allow_tail && c.occ == 1 ? last_round_subs(c.cfg, rem, slots) : 0;
+      const int sub = allow_tail && c.occ == 1 ? last_round_subs(gemm_dl_subs(c.cfg), rem, slots) : 0;
       double rounds = (double)full;
       if (sub)
         rounds += sub == 4 ? 0.55 : 0.75;
